@@ -19,7 +19,7 @@ constexpr int MIN_PARTIES = 2;
 constexpr int BLOCK = 256;          // threads per block of the element-wise kernels
 constexpr int WAVES = BLOCK / 64;   // wave64
 constexpr int MAX_SLOTS = 4096;     // per-block accumulator slots (upper bound on grid size)
-constexpr int64_t MAX_MFMA_K = 8191; // int32 class sums stay exact for inner dimension 2K <= 16382
+constexpr int64_t MAX_MFMA_K = 8191; // the matrix engine's moduli cover sums of 2K <= 16382 products
 
 // fields of a context
 enum FieldId : int { FID_61 = 0, FID_127 = 1, FID_32 = 2 };
@@ -64,7 +64,7 @@ struct spdz_ctx {
   bool validate = false;
   uint32_t *d_bad = nullptr;
   uint32_t *h_bad = nullptr;
-  // workspace of the matrix-triple product (digit planes, E F), grown on demand
+  // workspace of the matrix-triple product (residue planes, opened matrices), grown on demand
   void *ws = nullptr;
   size_t ws_bytes = 0;
   // kernel timing (spdz_timing_enable): HIP events around each main kernel

@@ -2,37 +2,38 @@
 // Z = C + D B + A E + D E of Sec. III-D, "MPC-specific optimization"; here the
 // opened matrices are called E = X - A and F = Y - B).
 //
-// For n parties the 4n + 1 mod-p matrix products are arranged as
-//   P      = E F                                   (once)
+// For n parties every output is one product over a concatenated inner dimension
+// 2K, with C added at the end.  The VALU engine computes P = E F once and then
 //   Z_i    = C_i    + [i = 0] P   + [E | A_i]    [B_i; F]
 //   M(Z)_i = M(C)_i + alpha_i P   + [E | M(A)_i] [M(B)_i; F]
-// so every output is one GEMM over a concatenated inner dimension 2K whose
-// initial value (C, P) is fused into the epilogue: 9 N^3 multiply-adds at
-// n = 2, no intermediate besides P.
+// (4n + 1 products); the matrix engine folds P into the right operands,
+//   Z_i    = C_i    + [E | A_i]    [B_i + [i = 0] F; F]
+//   M(Z)_i = M(C)_i + [E | M(A)_i] [M(B)_i + alpha_i F; F]
+// (4n products).
 //
-// Two GEMM engines compute the same exact integers mod p:
+// Two engines compute the same exact integers mod p:
 //   * VALU: 64 x 64 output tiles staged through LDS, 64 x 64 -> 128-bit
 //     products accumulated exactly in 128 bits and folded every 32 steps;
-//   * MFMA: each residue (< 2^61) is written as 8 balanced base-256 digits in
-//     [-128, 127]; the 64 digit-pair products run as v_mfma_i32_32x32x32_i8 and
-//     are summed per shift class s = k + l (15 classes, at most 8 pairs each)
-//     in int32, which is exact while 8 * K' * 2^14 < 2^31 (K' <= 16383); the
-//     classes are recombined mod p as rotations, 2^(8 s) = 2^(8 s mod 61).
+//   * matrix cores: the operands' residues modulo 17 or 18 coprime byte-sized
+//     moduli (rns.h), one exact int8 product per modulus with
+//     v_mfma_i32_32x32x32_i8, whose entries mod m_t are stored as bytes and
+//     joined by the Chinese remainder theorem.
 #include <string.h>
 
+#include <algorithm>
+
 #include "ctx.h"
+#include "rns.h"
 
 namespace spdz {
 
 constexpr int MAXOUT = 2 * MAX_PARTIES;
 constexpr int TILE = 64;
-constexpr int NDIG = 8;
-constexpr int SK = 64;  // inner-dimension depth of one MFMA LDS stage (planes are padded to it)
 
 struct GemmJob {
   int npairs;
-  const void *L[2];  // VALU: u64 [rows][K] (ld K); MFMA: tile-major int8 digit planes (Mp Kp bytes x 8)
-  const void *R[2];  // VALU: u64 [K][cols] (ld cols); MFMA: tile-major int8 digit planes (Np Kp bytes x 8)
+  const void *L[2];  // u64 [rows][K] (ld K)
+  const void *R[2];  // u64 [K][cols] (ld cols)
   const u64 *init;   // [M][N] canonical or null
   const u64 *pmat;   // [M][N] canonical or null, added times pscale
   u64 pscale;
@@ -41,8 +42,7 @@ struct GemmJob {
 
 struct GemmArgs {
   GemmJob job[MAXOUT];
-  int64_t M, N, K;   // K of each pair (true K; the MFMA planes are padded to Kp)
-  int64_t Mp, Np, Kp;
+  int64_t M, N, K;   // K of each pair
 };
 
 __device__ __forceinline__ u64 epilogue_add(u64 v, const GemmJob &j, int64_t idx) {
@@ -119,206 +119,354 @@ __global__ __launch_bounds__(256) void k_gemm_valu(const GemmArgs A) {
 }
 
 // --------------------------------------------------------------------------
-// digit planes: v = sum_{d<8} digit_d 256^d with digit_d in [-128, 127]
+// matrix engine: residue planes
+//
+// Planes of one operand panel: per modulus, per block of 64 plane rows (rows of a
+// left operand, columns of a right one) and per 64 inner indices one contiguous 4 KB
+// block [chunk 4][row 64][16 bytes].  A tile's operand stage is a few such blocks, moved to
+// LDS as they lie; zeros outside the matrix.  Which inner indices a chunk holds is free as long as
+// both operands agree: chunk c holds c, c + 4, ..., c + 60 of its 64, so that the four lanes with one
+// row of a left operand read along it.
 // --------------------------------------------------------------------------
-__device__ __forceinline__ void balanced_digits(u64 v, int8_t (&dg)[NDIG]) {
-  int carry = 0;
-#pragma unroll
-  for (int d = 0; d < NDIG; d++) {
-    int t = (int)((v >> (8 * d)) & 255u) + carry;
-    carry = t >= 128;
-    dg[d] = (int8_t)(t - (carry << 8));
-  }
+constexpr int PB = 4096;                          // bytes of one plane block
+constexpr int MAXSRC = 2 * (2 * MAX_PARTIES + 1); // planes kernel: operands of one launch
+
+__device__ __forceinline__ u32 pack4(int a, int b, int c, int d) {  // the low bytes of four ints
+  return __builtin_amdgcn_perm((u32)b, (u32)a, 0x0c0c0400u) | __builtin_amdgcn_perm((u32)d, (u32)c, 0x04000c0cu);
 }
 
-// Tile-major planes: for plane-row block b (64 rows) and stage s (64 inner indices),
-// the STAGE = 32 KB at (b (Kp / 64) + s) STAGE hold [digit 8][chunk 4][row 64][16 bytes];
-// byte j of (d, c, row) is digit d of the element at plane row 64 b + row and inner
-// index k = 64 s + 16 c + j.  One operand stage of one tile is thus one contiguous block.
-// LEFT: src [rows][cols] (ld = cols); plane row = source row, k = source column.
-// RIGHT: src [K][cols] (ld = cols); plane row = source column, k = source row.
-// One thread per (plane row, 16-deep chunk), consecutive threads on consecutive plane
-// rows (coalesced 16-byte writes; coalesced reads for RIGHT); zero padding outside the matrix.
-template <bool RIGHT>
-__global__ __launch_bounds__(256) void k_digits(const u64 *__restrict__ src, int64_t rows, int64_t cols,
-                                               int8_t *__restrict__ planes, int64_t Rp, int64_t Kp) {
-  const int64_t kchunks = Kp / 16, total = Rp * kchunks;
-  for (int64_t w = (int64_t)blockIdx.x * 256 + threadIdx.x; w < total; w += (int64_t)gridDim.x * 256) {
-    const int64_t pr = w % Rp, kc = w / Rp;
-    int8_t out[NDIG][16];
+struct PlaneSrc {
+  const u64 *src;   // LEFT: [rows][K]; RIGHT: [K][cols]; row-major
+  const u64 *add;   // nullable: scale * add joins src (same shape)
+  u64 scale;
+  int8_t *out;
+  int64_t ld;       // columns of src
+  int64_t r0, nrow; // first plane row of the panel, plane rows of the whole operand
+  int64_t rb;       // 64-row blocks of the panel
+  int right;
+};
+
+struct PlaneArgs {
+  PlaneSrc s[MAXSRC];
+  int64_t K, ks;    // inner dimension, 64-deep blocks of it
+};
+
+// One work item of 256 threads makes one plane block of every modulus: 64 plane rows x 64 inner
+// indices, a thread 16 of them of one row.  Left operands: lanes 4 chunks x 16 rows; right operands: a
+// wave one chunk of 64 consecutive columns.  blockIdx.y takes one operand, blockIdx.z one of gridDim.z
+// parts of the moduli.  Bound by memory: 8 bytes read and T written per element.  The loop over the
+// moduli is not unrolled: small products wait for the code itself.
+template <int T>
+__global__ __launch_bounds__(256) void k_planes(const PlaneArgs A) {
+  const PlaneSrc &S = A.s[blockIdx.y];
+  constexpr const rns::Tables &B = rns::tab<T>();
+  const int t256 = threadIdx.x, left = !S.right;
+  const int pr = left ? t256 >> 2 : t256 & 63, c = left ? t256 & 3 : t256 >> 6;
+  const int64_t step = S.rb * A.ks * PB;
+  const int per = (T + gridDim.z - 1) / gridDim.z, t0 = blockIdx.z * per, t1 = min(T, t0 + per);
+  for (int64_t item = blockIdx.x; item < S.rb * A.ks; item += gridDim.x) {
+    const int64_t rb = item % S.rb, kb = item / S.rb;
+    const int64_t row = S.r0 + rb * 64 + pr, k = kb * 64 + c;
+    const int64_t at = left ? row * S.ld + k : k * S.ld + row, da = left ? 4 : 4 * S.ld;
+    u64 d[16];
 #pragma unroll
     for (int j = 0; j < 16; j++) {
-      const int64_t k = kc * 16 + j;
-      u64 v = 0;
-      if (RIGHT) {
-        if (pr < cols && k < rows) v = src[k * cols + pr];
-      } else {
-        if (pr < rows && k < cols) v = src[pr * cols + k];
-      }
-      int8_t dg[NDIG];
-      balanced_digits(v, dg);
-#pragma unroll
-      for (int d = 0; d < NDIG; d++) out[d][j] = dg[d];
+      const bool in = row < S.nrow && k + 4 * j < A.K;
+      u64 v = in ? S.src[at + j * da] : 0;
+      if (S.add && in) v = F61::canon(F61::add(F61::E{v}, F61::mul(F61::E{S.scale}, F61::E{S.add[at + j * da]}))).v;
+      d[j] = rns::digits(v);
     }
+    int8_t *out = S.out + t0 * step + (rb * A.ks + kb) * PB + c * 1024 + pr * 16;
+#pragma unroll 1
+    for (int t = t0; t < t1; t++) {
+      const int c0 = (int)B.c0[left][t], c1 = (int)B.c1[left][t], bias = (int)B.bias[t], neg = B.neg[t];
+      const float inv = B.inv[t];
+      u32 pk[4];
 #pragma unroll
-    for (int d = 0; d < NDIG; d++) {
-      int4 pk;
-      __builtin_memcpy(&pk, out[d], 16);
-      const int64_t tile = (pr / TILE) * (Kp / SK) + kc / (SK / 16);
-      *reinterpret_cast<int4 *>(planes + tile * (NDIG * SK * TILE) + ((d * (SK / 16) + kc % (SK / 16)) * TILE + pr % TILE) * 16) = pk;
+      for (int q = 0; q < 4; q++) {
+        int r[4];
+#pragma unroll
+        for (int i = 0; i < 4; i++) {
+          const int j = 4 * q + i;
+          const int s = __builtin_amdgcn_sdot4((int)d[j], c0,
+                                               __builtin_amdgcn_sdot4((int)(d[j] >> 32), c1, bias, false), false);
+          r[i] = rns::round_mod((u32)s, inv, neg);
+        }
+        pk[q] = pack4(r[0], r[1], r[2], r[3]);
+      }
+      *reinterpret_cast<uint4 *>(out) = make_uint4(pk[0], pk[1], pk[2], pk[3]);
+      out += step;
     }
   }
 }
 
 // --------------------------------------------------------------------------
-// MFMA engine: 4 waves per block, 64 x 64 output tile, 32 x 32 per wave
+// matrix engine: the int8 products
 //
-// One operand stage of a tile (SK = 64 inner indices, 8 digits, 64 rows) is one
-// contiguous 32 KB block of the tile-major digit planes, ordered [digit][16-deep
-// chunk][row][16 bytes]; the 256 threads move it 16 bytes each per round (fully
-// coalesced, sequential addresses) straight from global memory into LDS in the same
-// order (no registers, no LDS store instructions), which makes the MFMA operand reads
-// (32 consecutive rows per half wave) conflict-free without padding.
+// 2 x 2 waves per block, each WM x WN subtiles of 32 x 32: a block's tile is 64 WM rows by
+// 64 WN columns of one output modulo one m_t.  Persistent blocks take tiles in turn; a ring of
+// NB stage buffers (64 inner indices of both operands) is filled straight from global memory
+// NB - 1 stages ahead, across tile ends too, so the next tile's operands arrive while the
+// last one's sums are reduced.  One barrier a stage: in its first half the waves multiply
+// operands read in the half before and read the second half's; then every wave waits for its
+// loads of the next stage and its LDS reads, so past the barrier the next stage is whole and
+// this stage's buffer is free; the second half multiplies, reads the next stage's first half
+// and refills the buffer.
+//
+// Bound by the matrix cores at the clock the chip's power allows.  M = K = N = 4096 at 2 parties (72
+// products of 4096 x 4096 x 8192): 7.7-7.9 ms, 2.5-2.6 POPS, matrix cores 78 % busy at 1.57 GHz; the
+// same kernel without its loads takes 6.6 ms and with products alone 6.2-6.3.  64 products of
+// base-256 digits, 64 x 64 outputs a block, took 27.5 ms for the same result.  Half-size tiles (two
+// blocks a CU, 1.5 times the operand traffic) take 8.3 ms, a quarter 11.9.
 // --------------------------------------------------------------------------
 typedef int v4i __attribute__((ext_vector_type(4)));
 typedef int v16i __attribute__((ext_vector_type(16)));
-constexpr int SCH = SK / 16;            // 16-byte chunks per row in a stage
-constexpr int RUN = TILE * 16;          // one (digit, chunk) run of a tile: 1 KB
-constexpr int STAGE = NDIG * SCH * RUN; // bytes per operand and stage: 32 KB
-
-__device__ __forceinline__ u64 rot61(u64 x, int t) {
-  return t == 0 ? x : (((x << t) | (x >> (61 - t))) & F61::P);
-}
-
-// Output tile of linear block b: jobs outermost; within a job, when both tile counts are
-// multiples of 16, each run of 256 consecutive blocks covers a 16 x 16 square of tiles and
-// the 32 of them that land on one XCD (blocks are dealt to the 8 XCDs in turn) a 4 x 8
-// patch, so an XCD's L2 holds 4 left and 8 right operand stages for 32 blocks; otherwise
-// row-major.
-__device__ __forceinline__ void tile_of(int b, int tx, int ty, int &bx, int &by, int &bz) {
-  const int per_z = tx * ty;
-  bz = b / per_z;
-  b -= bz * per_z;
-  if (tx % 16 == 0 && ty % 16 == 0) {
-    const int xcd = b % 8, slot = b / 8, g = slot / 32, r = slot % 32;
-    by = (g / (tx / 16)) * 16 + (xcd / 2) * 4 + r / 8;
-    bx = (g % (tx / 16)) * 16 + (xcd % 2) * 8 + r % 8;
-  } else {
-    bx = b % tx;
-    by = b / tx;
-  }
-}
-
 typedef __attribute__((address_space(3))) void *lds_ptr;
 
-// 16 bytes per lane from global memory straight into LDS: a wave's 64 lanes fill the 1 KB
-// at `wave_dst` (wave-uniform), lane l at wave_dst + 16 l
-__device__ __forceinline__ void to_lds(const int8_t *src, int8_t *wave_dst) {
-  __builtin_amdgcn_global_load_lds(src, (lds_ptr)wave_dst, 16, 0, 0);
+// 16 bytes per lane from base + uoff + loff straight into LDS: a wave's 64 lanes fill the 1 KB at
+// `wave_dst` (wave-uniform), lane l at wave_dst + 16 l.  The buffer form takes the uniform part of
+// the address from scalar registers, so a load costs no vector instruction beside itself.
+__device__ __forceinline__ void to_lds(const int8_t *base, u32 loff, u32 uoff, int8_t *wave_dst) {
+  __builtin_amdgcn_raw_ptr_buffer_load_lds(__builtin_amdgcn_make_buffer_rsrc((void *)base, 0, -1, 0x00027000),
+                                           (lds_ptr)wave_dst, 16, (int)loff, (int)uoff, 0, 0);
 }
 
-__global__ __launch_bounds__(256, 1) void k_gemm_mfma(const GemmArgs A) {
-  int bx, by, bz;
-  tile_of(blockIdx.x, (int)(A.Np / TILE), (int)(A.Mp / TILE), bx, by, bz);
-  const GemmJob &J = A.job[bz];
-  const int64_t r0 = (int64_t)by * TILE, c0 = (int64_t)bx * TILE;
-  // two stage buffers: stage s is read from buffer s & 1 while stage s + 1 is in flight
-  __shared__ __attribute__((aligned(16))) int8_t S[2][2][STAGE];  // [buffer][left | right]
-  const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+// waits until at most V of the wave's vector-memory operations are outstanding (they end in order)
+// and none of its LDS reads, then for the block
+template <int V>
+__device__ __forceinline__ void stage_barrier() {
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_sched_barrier(0);
+  __builtin_amdgcn_s_waitcnt((V & 15) | (V >> 4 << 14) | 0x70);  // vmcnt(V) lgkmcnt(0)
+  __builtin_amdgcn_s_barrier();
+  __builtin_amdgcn_sched_barrier(0);
+  asm volatile("" ::: "memory");
+}
+__device__ __forceinline__ void wait_lds() {
+  __builtin_amdgcn_s_waitcnt(0xc07f);  // lgkmcnt(0)
+  __builtin_amdgcn_sched_barrier(0);
+}
+
+struct RnsArgs {
+  const int8_t *L, *R;              // planes of the panel's left / right operands, source by source
+  int8_t *res;                      // bytes: [z][tile][t][wave][WM][WN][lane][16]
+  int lsrc[MAXOUT][2], rsrc[MAXOUT][2];  // operand pair q of output z
+  int nz, T, npairs, ks;
+  int64_t rbl, rbr;                 // 64-row blocks of the left / right panel
+  int tx, ty;                       // tiles of the panel
+};
+
+// Tile of rank w among tx x ty: groups of four tile rows, column by column within a group, so a
+// run of consecutive ranks (the tiles one XCD works on at a time) is a compact patch.
+__device__ __forceinline__ void tile_of(int w, int tx, int ty, int &bx, int &by) {
+  const int g = w / (4 * tx), r = w - g * 4 * tx, rows = min(4, ty - 4 * g);
+  bx = r / rows;
+  by = 4 * g + r - bx * rows;
+}
+
+template <int WM, int WN, int NB>
+__global__ __launch_bounds__(256, WM * WN >= 16 ? 1 : 2) void k_rns_gemm(const RnsArgs A) {
+  constexpr int NQ = WM + WN, SB = NQ * PB;  // plane blocks and bytes of a stage
+  __shared__ __attribute__((aligned(16))) int8_t S[NB * SB];
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int wr = wave >> 1, wc = wave & 1;
-  v16i acc[2 * NDIG - 1];
-#pragma unroll
-  for (int s = 0; s < 2 * NDIG - 1; s++) acc[s] = (v16i){0};
-  const int ks = (int)(A.Kp / SK), nst = J.npairs * ks;
-  // the stage s of tile row (column) block b is STAGE contiguous bytes at (b ks + s) STAGE;
-  // a fetch moves run q of it in eight rounds, 16 bytes per lane, into the same offsets of LDS
-  const int64_t toff = (int64_t)t * 16;
-  const int woff = wave * 1024;
-  const int8_t *gl = (const int8_t *)J.L[0] + (int64_t)by * ks * STAGE + toff;
-  const int8_t *gr = (const int8_t *)J.R[0] + (int64_t)bx * ks * STAGE + toff;
-  const int8_t *l1 = (const int8_t *)J.L[1] + (int64_t)by * ks * STAGE + toff;
-  const int8_t *r1 = (const int8_t *)J.R[1] + (int64_t)bx * ks * STAGE + toff;
-#pragma unroll
-  for (int q = 0; q < NDIG; q++) {
-    to_lds(gl + q * SCH * RUN, &S[0][0][q * SCH * RUN + woff]);
-    to_lds(gr + q * SCH * RUN, &S[0][1][q * SCH * RUN + woff]);
-  }
-  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-  __syncthreads();
-  // MFMA operands: lane supplies row (lane & 31) of its wave's 32 rows (columns) at chunk
-  // 2 kk + (lane >> 5); left and right use the same chunk, so the k pairing is consistent
-  const int aoff = ((lane >> 5) * TILE + wr * 32 + (lane & 31)) * 16;
-  const int boff = ((lane >> 5) * TILE + wc * 32 + (lane & 31)) * 16;
-  for (int st = 0; st < nst; st++) {
-    const int buf = st & 1;
-    // the next stage's operand blocks (the last stage re-reads its own: in bounds, unused)
-    const int nx = st + 1 < nst ? st + 1 : st;
-    if (nx != st) {
-      gl = nx == ks ? l1 : gl + STAGE;
-      gr = nx == ks ? r1 : gr + STAGE;
-    }
-    const int8_t *sl = &S[buf][0][0], *sr = &S[buf][1][0];
-    int8_t *wl = &S[buf ^ 1][0][0], *wrr = &S[buf ^ 1][1][0];
-    // operand reads: at most 13 LDS operations are outstanding at any MFMA group, so each
-    // group waits for exactly the reads it needs (the LDS counter field holds 15)
-    v4i a0[NDIG], b0[NDIG], a1[NDIG], b1[NDIG];
-#pragma unroll
-    for (int d = 0; d < NDIG; d++) b0[d] = *reinterpret_cast<const v4i *>(sr + (d * SCH) * RUN + boff);
-    a0[0] = *reinterpret_cast<const v4i *>(sl + aoff);
-    a0[1] = *reinterpret_cast<const v4i *>(sl + SCH * RUN + aoff);
-    // first half: each group of 8 MFMAs reads a first-half operand two groups ahead and two
-    // second-half operands, so the second half reads nothing from LDS
-#pragma unroll
-    for (int dk = 0; dk < NDIG; dk++) {
-      __builtin_amdgcn_sched_barrier(0);
-      if (dk + 2 < NDIG) a0[dk + 2] = *reinterpret_cast<const v4i *>(sl + ((dk + 2) * SCH) * RUN + aoff);
-      b1[dk] = *reinterpret_cast<const v4i *>(sr + (dk * SCH + 2) * RUN + boff);
-      a1[dk] = *reinterpret_cast<const v4i *>(sl + (dk * SCH + 2) * RUN + aoff);
-#pragma unroll
-      for (int dl = 0; dl < NDIG; dl++)
-        acc[dk + dl] = __builtin_amdgcn_mfma_i32_32x32x32_i8(a0[dk], b0[dl], acc[dk + dl], 0, 0, 0);
-    }
-    // second half: after each of its first four groups, four loads of the next stage into the
-    // other buffer (last read in stage st - 1, before every wave passed the previous barrier):
-    // the LDS takes them while it serves no operand reads, and the last four groups leave
-    // them time to land before the barrier
-#pragma unroll
-    for (int dk = 0; dk < NDIG; dk++) {
-      __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-      for (int dl = 0; dl < NDIG; dl++)
-        acc[dk + dl] = __builtin_amdgcn_mfma_i32_32x32x32_i8(a1[dk], b1[dl], acc[dk + dl], 0, 0, 0);
-      if (dk < NDIG / 2) {
-        __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int h = 0; h < 2; h++) {
-          const int d = 2 * dk + h;
-          to_lds(gl + d * SCH * RUN, wl + d * SCH * RUN + woff);
-          to_lds(gr + d * SCH * RUN, wrr + d * SCH * RUN + woff);
-        }
+  const int G = gridDim.x, total = A.nz * A.T * A.tx * A.ty, nst = A.npairs * A.ks;
+  // blocks are dealt to the 8 XCDs in turn: XCD x takes a run of G / 8 consecutive tiles of each G
+  int idx = G % 8 == 0 ? (int)(blockIdx.x % 8) * (G / 8) + (int)(blockIdx.x / 8) : (int)blockIdx.x;
+  const u32 lrow = (u32)A.ks * PB;  // bytes of one 64-row block (<= 128 * 4096)
+  const int8_t *lp, *rp;
+  int lidx = idx, pair = 0, left = A.ks;  // tile, operand pair and stages left of it of the next load
+  const u32 loff = threadIdx.x * 16;
+  auto point = [&](int id, int pr) {
+    const int per = A.tx * A.ty, gz = id / per, t = gz / A.nz, z = gz - t * A.nz;
+    int bx, by;
+    tile_of(id - gz * per, A.tx, A.ty, bx, by);
+    lp = A.L + (((int64_t)A.lsrc[z][pr] * A.T + t) * A.rbl + (int64_t)by * WM) * (int64_t)lrow;
+    rp = A.R + (((int64_t)A.rsrc[z][pr] * A.T + t) * A.rbr + (int64_t)bx * WN) * (int64_t)lrow;
+  };
+  // load q of the stage (blocks 0 .. WM - 1 left, then right) into the stage buffer at `buf`
+  auto load = [&](int q, int8_t *buf) {
+    to_lds(q < WM ? lp : rp, loff, (q < WM ? q : q - WM) * lrow, buf + q * PB + wave * 1024);
+  };
+  auto advance = [&]() {
+    if (__builtin_expect(--left == 0, 0)) {  // the second operand pair, or the next tile's first
+      left = A.ks;
+      if (++pair == A.npairs) {  // past the last tile its first stages are read again (unused)
+        pair = 0;
+        if (lidx + G < total) lidx += G;
       }
+      point(lidx, pair);
+    } else {
+      lp += PB;
+      rp += PB;
     }
-    __builtin_amdgcn_sched_barrier(0);
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the next stage has landed in LDS
-    __syncthreads();
+  };
+  point(idx, 0);
+#pragma unroll
+  for (int b = 0; b < NB - 1; b++) {
+#pragma unroll
+    for (int q = 0; q < NQ; q++) load(q, S + b * SB);
+    advance();
   }
-  // recombine the shift classes mod p, one output element at a time, and apply the epilogue
-  const int64_t M = A.M, N = A.N;
 #pragma unroll
-  for (int r = 0; r < 16; r++) {
-    u64 x = 0;
+  for (int q = 0; q < NQ / 2; q++) load(q, S + (NB - 1) * SB);
+  stage_barrier<(NB - 2) * NQ + NQ / 2>();
+  // MFMA operands: lane supplies row (lane & 31) of a 32-row subtile at chunk 2 kk + (lane >> 5);
+  // left and right use the same chunk, so the pairing of inner indices is consistent
+  const int lo = (lane >> 5) * 1024 + (lane & 31) * 16;
+  const int aoff = wr * (WM / 2) * PB + lo, boff = (WM + wc * (WN / 2)) * PB + lo;
+  auto rd = [&](const int8_t *base, int i, int kk) {
+    return *reinterpret_cast<const v4i *>(base + (i >> 1) * PB + (i & 1) * 512 + kk * 2048);
+  };
+  v4i a0[WM], b0[WN], a1[WM], b1[WN];
+  int cur = 0, prv = (NB - 1) * SB;  // byte offsets of the current stage's buffer and the one before
 #pragma unroll
-    for (int s = 0; s < 2 * NDIG - 1; s++) {
-      int cs = acc[s][r];
-      asm volatile("" : "+v"(cs));  // read the accumulator here, not hoisted across rows
-      const u64 m = cs < 0 ? (u64)((int64_t)cs + (int64_t)F61::P) : (u64)cs;  // |cs| < 2^31
-      x = F61::add(F61::E{x}, F61::E{rot61(m, (8 * s) % 61)}).v;
+  for (int i = 0; i < WM; i++) a0[i] = rd(S + aoff, i, 0);
+#pragma unroll
+  for (int j = 0; j < WN; j++) b0[j] = rd(S + boff, j, 0);
+  wait_lds();
+  // the load of a half that follows its product k, or -1: spread evenly
+  auto load_at = [](int k) constexpr { return (k + 1) * (NQ / 2) % (WM * WN) < NQ / 2 ? (k + 1) * (NQ / 2) / (WM * WN) - 1 : -1; };
+  for (; idx < total; idx += G) {
+    v16i acc[WM][WN];
+#pragma unroll
+    for (int i = 0; i < WM; i++)
+#pragma unroll
+      for (int j = 0; j < WN; j++) acc[i][j] = (v16i){0};
+    for (int st = 0; st < nst; st++) {
+      const int nxt = cur + SB == NB * SB ? 0 : cur + SB;
+      // behind each product at most one read (of what the next half multiplies) or one load (half a
+      // stage in each half): the matrix core takes 32 cycles a product, and a run of other
+      // instructions, or of loads in all four waves at once, would outlast it
+#pragma unroll
+      for (int k = 0; k < WM * WN; k++) {
+        acc[k / WN][k % WN] = __builtin_amdgcn_mfma_i32_32x32x32_i8(a0[k / WN], b0[k % WN], acc[k / WN][k % WN], 0, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
+        if (k < WN) b1[k] = rd(S + cur + boff, k, 1);
+        if (k >= WM * WN - WM - WN && k < WM * WN - WN) a1[k - (WM * WN - NQ)] = rd(S + cur + aoff, k - (WM * WN - NQ), 1);
+        if (load_at(k) >= 0) load(NQ / 2 + load_at(k), S + prv);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      advance();
+      stage_barrier<(NB - 2) * NQ>();
+#pragma unroll
+      for (int k = 0; k < WM * WN; k++) {
+        acc[k / WN][k % WN] = __builtin_amdgcn_mfma_i32_32x32x32_i8(a1[k / WN], b1[k % WN], acc[k / WN][k % WN], 0, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
+        if (k < WN) b0[k] = rd(S + nxt + boff, k, 0);
+        if (k >= WM * WN - WM - WN && k < WM * WN - WN) a0[k - (WM * WN - NQ)] = rd(S + nxt + aoff, k - (WM * WN - NQ), 0);
+        if (load_at(k) >= 0) load(load_at(k), S + cur);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      wait_lds();
+      prv = cur;
+      cur = nxt;
     }
-    const int row = 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
-    const int col = lane & 31;
-    const int64_t gr = r0 + wr * 32 + row, gc = c0 + wc * 32 + col;
-    if (gr < M && gc < N) J.out[gr * N + gc] = epilogue_add(x, J, gr * N + gc);
-    __builtin_amdgcn_sched_barrier(0);  // keep each element's 15 conversions together
+    if constexpr (WM * WN >= 16) {  // the sums stay in the accumulation registers until each is read below
+#pragma unroll
+      for (int i = 0; i < WM; i++)
+#pragma unroll
+        for (int j = 0; j < WN; j++) asm volatile("" : "+a"(acc[i][j]));
+    }
+    // the sums mod m_t, a byte each (|sum| <= 16382 * 127^2 < 2^28)
+    const int per = A.tx * A.ty, gz = idx / per, t = gz / A.nz, z = gz - t * A.nz;
+    const float inv = rns::TAB18.inv[t];
+    const int neg = rns::TAB18.neg[t], c14 = rns::TAB18.c14[t];
+    const u32 bias14 = rns::TAB18.bias14[t];
+    int8_t *out = A.res + (((int64_t)z * per + (idx - gz * per)) * A.T + t) * (64 * 64 * WM * WN) +
+                  wave * (WM * WN * 1024) + lane * 16;
+#pragma unroll
+    for (int i = 0; i < WM; i++)
+#pragma unroll
+      for (int j = 0; j < WN; j++) {
+        u32 pk[4];
+#pragma unroll
+        for (int q = 0; q < 4; q++) {
+          int r[4];
+#pragma unroll
+          for (int e = 0; e < 4; e++) {
+            int x = acc[i][j][4 * q + e];
+            asm volatile("" : "+v"(x));  // read the accumulator here, not hoisted across subtiles
+            r[e] = rns::round_mod28(x, inv, neg, c14, bias14);
+          }
+          pk[q] = pack4(r[0], r[1], r[2], r[3]);
+        }
+        *reinterpret_cast<uint4 *>(out + (i * WN + j) * 1024) = make_uint4(pk[0], pk[1], pk[2], pk[3]);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+  }
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // no load of this block lands after its LDS is given away
+}
+
+// --------------------------------------------------------------------------
+// matrix engine: the T bytes of every output element joined mod p, plus C
+//
+// One thread per 4 elements of a subtile, in the order the products are stored: every load a
+// contiguous 256 bytes per wave, C and Z in runs of 128.  Bound by memory: T bytes, C and Z per
+// element, 0.40-0.42 ms for 4 outputs of 4096^2 (5.5 TB/s; 16 elements a thread: 0.46).
+struct CrtArgs {
+  const int8_t *res;
+  const u64 *init[MAXOUT];  // canonical or null
+  u64 *out[MAXOUT];
+  int64_t M, N, r0, c0;     // output shape, first row and column of the panel
+  int tx, ty;
+};
+
+template <int T, int WM, int WN>
+__global__ __launch_bounds__(256) void k_crt(const CrtArgs A) {
+  constexpr const rns::Tables &B = rns::tab<T>();
+  constexpr int TB = 64 * 64 * WM * WN, SUBS = 4 * WM * WN;  // bytes of a tile per modulus, its subtiles
+  const int z = blockIdx.y, lane = threadIdx.x >> 2, q = threadIdx.x & 3;
+  const int64_t nsub = (int64_t)A.tx * A.ty * SUBS;
+  const u64 *init = A.init[z];
+  u64 *out = A.out[z];
+  for (int64_t s = blockIdx.x; s < nsub; s += gridDim.x) {
+    const int tile = (int)(s / SUBS), sub = (int)(s % SUBS);
+    int bx, by;
+    tile_of(tile, A.tx, A.ty, bx, by);
+    const int wave = sub / (WM * WN), i = sub / WN % WM, j = sub % WN;
+    const int64_t row0 = A.r0 + (int64_t)by * 64 * WM + (wave >> 1) * 32 * WM + i * 32 + 8 * q + 4 * (lane >> 5);
+    const int64_t col = A.c0 + (int64_t)bx * 64 * WN + (wave & 1) * 32 * WN + j * 32 + (lane & 31);
+    const int8_t *p = A.res + ((int64_t)z * A.tx * A.ty + tile) * T * TB + (int64_t)sub * 1024 + threadIdx.x * 4;
+    u64 ini[4];  // requested with the bytes
+#pragma unroll
+    for (int e = 0; e < 4; e++)
+      ini[e] = init && row0 + e < A.M && col < A.N ? __builtin_nontemporal_load(init + (row0 + e) * A.N + col) : 0;
+    u32 by4[5][4];  // bytes of four moduli of one element, offset by 128
+    u32 v[20];
+#pragma unroll
+    for (int t = 0; t < 20; t++) v[t] = t < T ? *reinterpret_cast<const u32 *>(p + (int64_t)t * TB) ^ 0x80808080u : 0u;
+#pragma unroll
+    for (int g = 0; g < 5; g++) {  // 4 x 4 byte transposes
+      const u32 *w = v + 4 * g;
+      const u32 a = __builtin_amdgcn_perm(w[1], w[0], 0x05010400u), b = __builtin_amdgcn_perm(w[3], w[2], 0x05010400u);
+      const u32 c = __builtin_amdgcn_perm(w[1], w[0], 0x07030602u), d = __builtin_amdgcn_perm(w[3], w[2], 0x07030602u);
+      by4[g][0] = __builtin_amdgcn_perm(b, a, 0x05040100u);
+      by4[g][1] = __builtin_amdgcn_perm(b, a, 0x07060302u);
+      by4[g][2] = __builtin_amdgcn_perm(d, c, 0x05040100u);
+      by4[g][3] = __builtin_amdgcn_perm(d, c, 0x07060302u);
+    }
+#pragma unroll
+    for (int e = 0; e < 4; e++) {
+      const int64_t row = row0 + e;
+      u32 D[8] = {0, 0, 0, 0, 0, 0, 0, 0}, f[2] = {0, 0};
+#pragma unroll
+      for (int g = 0; g < 5; g++) {
+#pragma unroll
+        for (int k = 0; k < 8; k++) D[k] = __builtin_amdgcn_udot4(by4[g][e], B.w[g][k], D[k], false);
+#pragma unroll
+        for (int k = 0; k < 2; k++) f[k] = __builtin_amdgcn_udot4(by4[g][e], B.f[g][k], f[k], false);
+      }
+      const int qq = ((int)(f[0] + (f[1] << 8) - B.fsum) + (1 << (rns::FRAC - 1))) >> rns::FRAC;  // |qq| <= 12
+      // each D below 2^21, so either half below 2^46
+      const u64 l = (u64)D[0] + ((u64)D[1] << 8) + ((u64)D[2] << 16) + ((u64)D[3] << 24);
+      const u64 h = (u64)D[4] + ((u64)D[5] << 8) + ((u64)D[6] << 16) + ((u64)D[7] << 24);
+      // h 2^32 = (h mod 2^29) 2^32 + (h >> 29) mod p
+      const u64 s61 = F61::fold(((h & ((1ull << 29) - 1)) << 32) + (h >> 29) + l);
+      F61::E x = F61::add(F61::E{s61}, F61::mul_small(F61::E{B.mp}, (u32)(16 - qq)));
+      x = F61::add(x, F61::E{B.wsum});
+      if (row < A.M && col < A.N) F61::store(out, 0, row * A.N + col, F61::add(x, F61::E{ini[e]}));
+    }
   }
 }
 
@@ -342,16 +490,161 @@ namespace {
 
 int64_t up(int64_t x, int64_t m) { return (x + m - 1) / m * m; }
 
-spdz_status digits(spdz_ctx *c, const u64 *src, int64_t rows, int64_t cols, int8_t *planes, int64_t Rp, int64_t Kp,
-                   bool right) {
-  const int64_t work = Rp * (Kp / 16);
-  int64_t g = (work + 255) / 256;
-  if (g > 65535) g = 65535;
-  if (right)
-    hipLaunchKernelGGL((k_digits<true>), dim3((unsigned)g), dim3(256), 0, c->stream, src, rows, cols, planes, Rp, Kp);
-  else
-    hipLaunchKernelGGL((k_digits<false>), dim3((unsigned)g), dim3(256), 0, c->stream, src, rows, cols, planes, Rp, Kp);
+spdz_status valu_gemm(spdz_ctx *c, const GemmArgs &G, int nout) {
+  dim3 grid((unsigned)((G.N + TILE - 1) / TILE), (unsigned)((G.M + TILE - 1) / TILE), (unsigned)nout);
+  KTimer tm(c, "matmul_valu");
+  hipLaunchKernelGGL(k_gemm_valu, grid, dim3(256), 0, c->stream, G);
   return hip_status(hipGetLastError());
+}
+
+// one operand of the matrix engine: src + scale add (add nullable), row-major
+struct RnsOperand {
+  const u64 *src, *add;
+  u64 scale;
+};
+
+// outputs z < nz: init + sum over pairs q of L[lsrc[z][q]] R[rsrc[z][q]] mod p, of M x N over K
+struct RnsProblem {
+  int64_t M, K, N;
+  int nl, nr, nz, npairs;
+  RnsOperand L[2 * MAX_PARTIES + 1], R[2 * MAX_PARTIES + 1];
+  int lsrc[MAXOUT][2], rsrc[MAXOUT][2];
+  const u64 *init[MAXOUT];
+  u64 *out[MAXOUT];
+};
+
+// workspace of a panel of pm rows and pn columns (whole tiles of tm x tn)
+struct RnsPlan {
+  int64_t pm, pn;           // panel size
+  size_t lbytes, rbytes, sbytes;
+};
+
+// largest workspace taken without trying panels
+constexpr size_t RNS_WS = (size_t)8 << 30;
+
+RnsPlan rns_plan(const RnsProblem &P, int T, int tm, int tn, int64_t pm, int64_t pn) {
+  const int64_t kp = up(P.K, 64);
+  return RnsPlan{pm, pn, (size_t)P.nl * T * pm * kp, (size_t)P.nr * T * pn * kp, (size_t)P.nz * T * pm * pn};
+}
+
+template <int T, int WM, int WN, int NB>
+spdz_status rns_panels(spdz_ctx *c, const RnsProblem &P, const RnsPlan &plan, char *ws, int bpc) {
+  int8_t *lp = (int8_t *)ws, *rp = lp + plan.lbytes, *res = rp + plan.rbytes;
+  const int64_t ks = up(P.K, 64) / 64;
+  RnsArgs G;
+  memset(&G, 0, sizeof(G));
+  G.L = lp;
+  G.R = rp;
+  G.res = res;
+  memcpy(G.lsrc, P.lsrc, sizeof(G.lsrc));
+  memcpy(G.rsrc, P.rsrc, sizeof(G.rsrc));
+  G.nz = P.nz;
+  G.T = T;
+  G.npairs = P.npairs;
+  G.ks = (int)ks;
+  CrtArgs R;
+  memset(&R, 0, sizeof(R));
+  R.res = res;
+  memcpy(R.init, P.init, sizeof(R.init));
+  memcpy(R.out, P.out, sizeof(R.out));
+  R.M = P.M;
+  R.N = P.N;
+  for (int64_t c0 = 0; c0 < P.N; c0 += plan.pn) {
+    const int64_t wn = up(std::min(plan.pn, P.N - c0), 64 * WN);
+    for (int64_t r0 = 0; r0 < P.M; r0 += plan.pm) {
+      const int64_t wm = up(std::min(plan.pm, P.M - r0), 64 * WM);
+      PlaneArgs A;
+      memset(&A, 0, sizeof(A));
+      A.K = P.K;
+      A.ks = ks;
+      int ns = 0;
+      for (int i = 0; i < P.nl; i++)
+        A.s[ns++] = PlaneSrc{P.L[i].src, P.L[i].add, P.L[i].scale, lp + (size_t)i * T * wm * ks * 64, P.K, r0, P.M,
+                             wm / 64, 0};
+      if (r0 == 0)  // the right operands' planes serve every row panel of the column panel
+        for (int i = 0; i < P.nr; i++)
+          A.s[ns++] = PlaneSrc{P.R[i].src, P.R[i].add, P.R[i].scale, rp + (size_t)i * T * wn * ks * 64, P.N, c0, P.N,
+                               wn / 64, 1};
+      {
+        const int64_t items = std::max(wm, wn) / 64 * ks;
+        // few work items: the moduli are split, up to six ways, for about four blocks a CU
+        const int64_t parts = std::min<int64_t>(6, std::max<int64_t>(1, 4 * (int64_t)c->num_cus / (items * ns)));
+        KTimer tm(c, "matmul_planes");
+        hipLaunchKernelGGL((k_planes<T>), dim3((unsigned)std::min<int64_t>(items, 65535), (unsigned)ns, (unsigned)parts),
+                           dim3(256), 0, c->stream, A);
+      }
+      SPDZ_RET(hip_status(hipGetLastError()));
+      G.rbl = wm / 64;
+      G.rbr = wn / 64;
+      G.tx = R.tx = (int)(wn / (64 * WN));
+      G.ty = R.ty = (int)(wm / (64 * WM));
+      R.r0 = r0;
+      R.c0 = c0;
+      const int64_t tiles = (int64_t)G.tx * G.ty;
+      const int64_t grid = std::min<int64_t>(tiles * P.nz * T, (int64_t)c->num_cus * bpc);
+      {
+        KTimer tm(c, "matmul_mfma");
+        hipLaunchKernelGGL((k_rns_gemm<WM, WN, NB>), dim3((unsigned)grid), dim3(256), 0, c->stream, G);
+      }
+      SPDZ_RET(hip_status(hipGetLastError()));
+      {
+        KTimer tm(c, "matmul_crt");
+        hipLaunchKernelGGL((k_crt<T, WM, WN>),
+                           dim3((unsigned)std::min<int64_t>(tiles * WM * WN, 65535), (unsigned)P.nz), dim3(256), 0,
+                           c->stream, R);
+      }
+      SPDZ_RET(hip_status(hipGetLastError()));
+    }
+  }
+  return SPDZ_OK;
+}
+
+// Runs the problem behind `head` bytes of the context workspace (grown as needed), after open(ws),
+// which enqueues what makes its operands.  A problem whose planes and bytes would take more than
+// RNS_WS runs in panels of whole tiles; where even that is not to be had, in smaller ones.
+template <int T, int WM, int WN, int NB, class Open>
+spdz_status rns_run(spdz_ctx *c, RnsProblem &P, size_t head, int bpc, Open &&open) {
+  constexpr int tm = 64 * WM, tn = 64 * WN;
+  int64_t pm = up(P.M, tm), pn = up(P.N, tn);
+  for (;;) {
+    const RnsPlan plan = rns_plan(P, T, tm, tn, pm, pn);
+    const size_t need = head + plan.lbytes + plan.rbytes + plan.sbytes;
+    const bool last = pm == tm && pn == tn;
+    if (need <= RNS_WS + head || last) {
+      const spdz_status s = ensure_ws(c, need);
+      if (s == SPDZ_OK) {
+        char *ws = (char *)c->ws;
+        SPDZ_RET(open(ws));
+        return rns_panels<T, WM, WN, NB>(c, P, plan, ws + head, bpc);
+      }
+      if (s != SPDZ_E_NOMEM || last) return s;
+    }
+    if (pm >= pn) pm = up((pm + 1) / 2, tm);
+    else pn = up((pn + 1) / 2, tn);
+  }
+}
+
+template <class Open>
+spdz_status rns_product(spdz_ctx *c, RnsProblem &P, size_t head, Open &&open) {
+  auto go = [&](auto tt) -> spdz_status {
+    constexpr int T = decltype(tt)::value;
+    // Relative time of a tiling: whole rounds of the resident blocks, each as long as its tile's products
+    // and the reduction of its sums (in inner indices: 340 where one block a CU leaves the matrix cores
+    // idle meanwhile, half where a second one fills them), over the rate the tile reaches (M = N = 2048
+    // at 2 parties: 0.99, 1.05 and 1.20 ms; 1800 x 100 x 1800 at 4: 301, 228 and 249 us; 300 x 1362 x 160
+    // at 2: 36, 34 and 24 us).
+    auto cost = [&](int wm, int wn, int bpc, double idle, double rate) {
+      const int64_t tiles = (P.M + 64 * wm - 1) / (64 * wm) * ((P.N + 64 * wn - 1) / (64 * wn)) * P.nz * T;
+      const int64_t slots = (int64_t)c->num_cus * bpc, rounds = (tiles + slots - 1) / slots;
+      return (double)(rounds * slots) * wm * wn * ((double)P.K * P.npairs + idle) / rate;
+    };
+    const double c44 = cost(4, 4, 1, 340, 1.0), c42 = cost(4, 2, 2, 170, 0.93), c22 = cost(2, 2, 2, 170, 0.8);
+    if (c44 <= c42 && c44 <= c22) return rns_run<T, 4, 4, 4>(c, P, head, 1, open);
+    if (c42 <= c22) return rns_run<T, 4, 2, 3>(c, P, head, 2, open);
+    return rns_run<T, 2, 2, 4>(c, P, head, 2, open);
+  };
+  if (P.K * P.npairs <= rns::T17_TERMS) return go(std::integral_constant<int, 17>{});
+  return go(std::integral_constant<int, 18>{});
 }
 
 }  // namespace
@@ -360,101 +653,83 @@ spdz_status launch_matmul_triple(spdz_ctx *c, int64_t M, int64_t K, int64_t N, c
                                  const spdz_shares *Y, const spdz_triple *T, spdz_shares *Z, u64 *E_pub, u64 *F_pub,
                                  int variant) {
   const int n = c->n;
-  const int64_t Mp = up(M, TILE), Np = up(N, TILE), Kp = up(K, SK), Kpm = up(K, TILE);
-  // workspace: [E][F][P] (u64) if not supplied, then digit planes when the MFMA engine runs
+  // workspace: the opened matrices if not supplied and, for the VALU engine, P; then the matrix engine's
   auto al = [](size_t b) { return (b + 255) / 256 * 256; };
-  const size_t e_bytes = al((size_t)M * K * 8), f_bytes = al((size_t)K * N * 8), p_bytes = al((size_t)M * N * 8);
-  const size_t lplane = (size_t)NDIG * Mp * Kp, rplane = (size_t)NDIG * Np * Kp;
-  // left planes: E, A_i, M(A)_i; right planes: F, B_i, M(B)_i
-  const size_t mfma_bytes = variant == 1 ? (1 + 2 * (size_t)n) * (lplane + rplane) : 0;
-  (void)Kpm;
-  const size_t need = e_bytes + f_bytes + p_bytes + mfma_bytes + 256;
-  SPDZ_RET(ensure_ws(c, need));
-  char *ws = (char *)c->ws;
-  u64 *E = E_pub ? E_pub : (u64 *)ws;
-  u64 *Fm = F_pub ? F_pub : (u64 *)(ws + e_bytes);
-  u64 *P = (u64 *)(ws + e_bytes + f_bytes);
-  int8_t *planes = (int8_t *)(ws + e_bytes + f_bytes + p_bytes);
-
-  // open E = X - A (row-major, M K values) then F = Y - B (K N values)
-  SPDZ_RET(launch_open_diff(c, X, &T->a, E));
-  SPDZ_RET(launch_open_diff(c, Y, &T->b, Fm));
-
+  const size_t e_bytes = E_pub ? 0 : al((size_t)M * K * 8), f_bytes = F_pub ? 0 : al((size_t)K * N * 8);
+  const size_t p_bytes = variant == 1 ? 0 : al((size_t)M * N * 8), head = e_bytes + f_bytes + p_bytes;
+  u64 *E = E_pub, *Fm = F_pub;
+  // opens E = X - A (row-major, M K values), then F = Y - B (K N values)
+  auto open = [&](char *ws) -> spdz_status {
+    if (!E) E = (u64 *)ws;
+    if (!Fm) Fm = (u64 *)(ws + e_bytes);
+    SPDZ_RET(launch_open_diff(c, X, &T->a, E));
+    return launch_open_diff(c, Y, &T->b, Fm);
+  };
+  auto a_of = [&](int i, bool mac) { return (mac ? T->a.mac : T->a.val) + i * T->a.party_stride; };
+  auto b_of = [&](int i, bool mac) { return (mac ? T->b.mac : T->b.val) + i * T->b.party_stride; };
+  auto c_of = [&](int i, bool mac) { return (mac ? T->c.mac : T->c.val) + i * T->c.party_stride; };
+  auto z_of = [&](int i, bool mac) { return (mac ? Z->mac : Z->val) + i * Z->party_stride; };
+  if (variant == 1) {
+    RnsProblem P;
+    memset(&P, 0, sizeof(P));
+    P.M = M;
+    P.K = K;
+    P.N = N;
+    P.nl = P.nr = 1 + 2 * n;
+    P.nz = 2 * n;
+    P.npairs = 2;
+    for (int z = 0; z < 2 * n; z++) {
+      P.lsrc[z][0] = P.rsrc[z][1] = 0;  // E, F
+      P.lsrc[z][1] = P.rsrc[z][0] = 1 + z;
+      P.init[z] = c_of(z % n, z >= n);
+      P.out[z] = z_of(z % n, z >= n);
+    }
+    return rns_product(c, P, head, [&](char *ws) -> spdz_status {
+      SPDZ_RET(open(ws));
+      P.L[0] = RnsOperand{E, nullptr, 0};
+      P.R[0] = RnsOperand{Fm, nullptr, 0};
+      for (int z = 0; z < 2 * n; z++) {
+        const int i = z % n;
+        P.L[1 + z] = RnsOperand{a_of(i, z >= n), nullptr, 0};
+        P.R[1 + z] = RnsOperand{b_of(i, z >= n), z == 0 || z >= n ? Fm : nullptr,
+                                z >= n ? F61::canon(F61::E{c->alpha[i][0]}).v : 1};
+      }
+      return SPDZ_OK;
+    });
+  }
+  SPDZ_RET(ensure_ws(c, head));
+  SPDZ_RET(open((char *)c->ws));
+  u64 *P = (u64 *)((char *)c->ws + e_bytes + f_bytes);
   GemmArgs G;
   memset(&G, 0, sizeof(G));
   G.M = M;
   G.N = N;
   G.K = K;
-  G.Mp = Mp;
-  G.Np = Np;
-  G.Kp = Kp;
-  const void *Lsrc[2 * MAX_PARTIES + 1], *Rsrc[2 * MAX_PARTIES + 1];
-  if (variant == 1) {
-    // plane sets: left 0 = E, 1 + i = A_i, 1 + n + i = M(A)_i; right likewise with F, B_i, M(B)_i
-    int8_t *lp = planes, *rp = planes + (1 + 2 * (size_t)n) * lplane;
-    SPDZ_RET(digits(c, E, M, K, lp, Mp, Kp, false));
-    SPDZ_RET(digits(c, Fm, K, N, rp, Np, Kp, true));
-    for (int i = 0; i < n; i++) {
-      SPDZ_RET(digits(c, T->a.val + i * T->a.party_stride, M, K, lp + (1 + i) * lplane, Mp, Kp, false));
-      SPDZ_RET(digits(c, T->a.mac + i * T->a.party_stride, M, K, lp + (1 + n + i) * lplane, Mp, Kp, false));
-      SPDZ_RET(digits(c, T->b.val + i * T->b.party_stride, K, N, rp + (1 + i) * rplane, Np, Kp, true));
-      SPDZ_RET(digits(c, T->b.mac + i * T->b.party_stride, K, N, rp + (1 + n + i) * rplane, Np, Kp, true));
-    }
-    for (int s = 0; s < 1 + 2 * n; s++) {
-      Lsrc[s] = lp + s * lplane;
-      Rsrc[s] = rp + s * rplane;
-    }
-  } else {
-    Lsrc[0] = E;
-    Rsrc[0] = Fm;
-    for (int i = 0; i < n; i++) {
-      Lsrc[1 + i] = T->a.val + i * T->a.party_stride;
-      Lsrc[1 + n + i] = T->a.mac + i * T->a.party_stride;
-      Rsrc[1 + i] = T->b.val + i * T->b.party_stride;
-      Rsrc[1 + n + i] = T->b.mac + i * T->b.party_stride;
-    }
-  }
-  auto launch = [&](int nout, const char *name) -> spdz_status {
-    dim3 grid((unsigned)(Np / TILE), (unsigned)(Mp / TILE), (unsigned)nout);
-    KTimer tm(c, name);
-    if (variant == 1)
-      hipLaunchKernelGGL(k_gemm_mfma, dim3(grid.x * grid.y * grid.z), dim3(256), 0, c->stream, G);
-    else
-      hipLaunchKernelGGL(k_gemm_valu, grid, dim3(256), 0, c->stream, G);
-    return hip_status(hipGetLastError());
-  };
   // P = E F
-  G.job[0] = GemmJob{1, {Lsrc[0], nullptr}, {Rsrc[0], nullptr}, nullptr, nullptr, 0, P};
-  SPDZ_RET(launch(1, variant == 1 ? "matmul_mfma" : "matmul_valu"));
+  G.job[0] = GemmJob{1, {E, nullptr}, {Fm, nullptr}, nullptr, nullptr, 0, P};
+  SPDZ_RET(valu_gemm(c, G, 1));
   // Z_i and M(Z)_i
   for (int i = 0; i < n; i++) {
-    G.job[i] = GemmJob{2, {Lsrc[0], Lsrc[1 + i]}, {Rsrc[1 + i], Rsrc[0]}, T->c.val + i * T->c.party_stride,
-                       i == 0 ? P : nullptr, 1, Z->val + i * Z->party_stride};
-    G.job[n + i] = GemmJob{2, {Lsrc[0], Lsrc[1 + n + i]}, {Rsrc[1 + n + i], Rsrc[0]}, T->c.mac + i * T->c.party_stride,
-                           P, F61::canon(F61::E{c->alpha[i][0]}).v, Z->mac + i * Z->party_stride};
+    G.job[i] = GemmJob{2, {E, a_of(i, false)}, {b_of(i, false), Fm}, c_of(i, false), i == 0 ? P : nullptr, 1,
+                       z_of(i, false)};
+    G.job[n + i] = GemmJob{2, {E, a_of(i, true)}, {b_of(i, true), Fm}, c_of(i, true), P,
+                           F61::canon(F61::E{c->alpha[i][0]}).v, z_of(i, true)};
   }
-  return launch(2 * n, variant == 1 ? "matmul_mfma" : "matmul_valu");
+  return valu_gemm(c, G, 2 * n);
 }
 
 // C = A B mod p for public matrices (used by the dealer of matrix triples)
 spdz_status launch_public_matmul(spdz_ctx *c, int64_t M, int64_t K, int64_t N, const u64 *Am, const u64 *Bm, u64 *Cm) {
-  const int64_t Mp = up(M, TILE), Np = up(N, TILE), Kp = up(K, SK);
-  const size_t lplane = (size_t)NDIG * Mp * Kp, rplane = (size_t)NDIG * Np * Kp;
-  SPDZ_RET(ensure_ws(c, lplane + rplane + 256));
-  int8_t *lp = (int8_t *)c->ws, *rp = lp + lplane;
-  SPDZ_RET(digits(c, Am, M, K, lp, Mp, Kp, false));
-  SPDZ_RET(digits(c, Bm, K, N, rp, Np, Kp, true));
-  GemmArgs G;
-  memset(&G, 0, sizeof(G));
-  G.M = M;
-  G.N = N;
-  G.K = K;
-  G.Mp = Mp;
-  G.Np = Np;
-  G.Kp = Kp;
-  G.job[0] = GemmJob{1, {lp, nullptr}, {rp, nullptr}, nullptr, nullptr, 0, Cm};
-  hipLaunchKernelGGL(k_gemm_mfma, dim3((unsigned)((Np / TILE) * (Mp / TILE))), dim3(256), 0, c->stream, G);
-  return hip_status(hipGetLastError());
+  RnsProblem P;
+  memset(&P, 0, sizeof(P));
+  P.M = M;
+  P.K = K;
+  P.N = N;
+  P.nl = P.nr = P.nz = P.npairs = 1;
+  P.L[0] = RnsOperand{Am, nullptr, 0};
+  P.R[0] = RnsOperand{Bm, nullptr, 0};
+  P.out[0] = Cm;
+  return rns_product(c, P, 0, [](char *) { return SPDZ_OK; });
 }
 
 }  // namespace spdz

@@ -131,3 +131,62 @@ def test_matmul_4096_sampled_and_freivalds():
     assert np.array_equal(lhs, rhs)
     a = sum(int(D.alpha[i, 0]) for i in range(n)) % P61
     assert np.array_equal(f.matmul(MZs, v), f.scale_public(a, rhs.reshape(1, -1)).reshape(Nn, 20))
+
+
+@pytest.mark.parametrize("n,M,K,N", [
+    (2, 40, 2143, 30), (2, 40, 2144, 30),    # 17 moduli up to 2 K = 4287, then 18
+    (2, 129, 63, 257), (3, 64, 65, 129),     # one past a tile, inner dimension around a plane block
+    (2, 1281, 70, 1030),                     # several rounds of 256-wide tiles, ragged in both directions
+    (8, 33, 5, 31), (5, 257, 1, 255),
+])
+def test_matmul_matrix_engine_shapes(n, M, K, N):
+    """Sizes at the edges of the matrix engine's moduli, tiles and plane blocks, all entries."""
+    D = deal_matrices(P61, n, M, K, N, 4)
+    ref = matrix_triple_run(D, check_seed=4)
+    Z, E, Fo, ok, sigma = run_device(D, 1, 4)
+    assert np.array_equal(host(E), ref["E"]) and np.array_equal(host(Fo), ref["F"])
+    assert np.array_equal(host(Z.val), ref["Z"].val) and np.array_equal(host(Z.mac), ref["Z"].mac)
+    assert ok and sigma == ints_of_sigma(ref["sigma"])
+
+
+@pytest.mark.parametrize("K,word", [(2143, (1 << 60) - 1), (2143, 1 << 60), (8191, (1 << 60) - 1), (8191, 1 << 60)])
+def test_matmul_largest_sums(K, word):
+    """Every opened and shared word at the largest balanced magnitude: sums next to the bound of the
+    moduli (X - A = Y - B = word, so that no product cancels)."""
+    from oracle.pipelines import DealtMat
+    n, M, N = 2, 3, 5
+    f = F.Field(P61)
+
+    def sh(first, rows, cols):
+        a = np.full((n, 1, rows * cols), 0, dtype=np.uint64)
+        a[0] = first
+        return F.Shares(a, a.copy())
+    al = np.array([[1], [0]], dtype=np.uint64)
+    X, A = sh((2 * word) % P61, M, K), F.Shares(*(np.full((n, 1, M * K), word, dtype=np.uint64) for _ in range(2)))
+    Y, B = sh((2 * word) % P61, K, N), F.Shares(*(np.full((n, 1, K * N), word, dtype=np.uint64) for _ in range(2)))
+    A.val[1] = A.mac[1] = B.val[1] = B.mac[1] = 0
+    C = F.Shares(np.zeros((n, 1, M * N), dtype=np.uint64), np.zeros((n, 1, M * N), dtype=np.uint64))
+    D = DealtMat(f, n, 0, M, K, N, al, None, X, None, Y, F.TripleArr(A, B, C))
+    ref = matrix_triple_run(D, check_seed=6)
+    Z, E, Fo, ok, sigma = run_device(D, 1, 6)
+    assert np.array_equal(host(Z.val), ref["Z"].val) and np.array_equal(host(Z.mac), ref["Z"].mac)
+    assert ok == ref["ok"] and sigma == ints_of_sigma(ref["sigma"])
+
+
+def test_matmul_panels_match_valu_engine():
+    """A product whose planes exceed the workspace bound runs in panels; the VALU engine gives the same shares."""
+    from paper_2512_11112_amd import spdz as S
+    n, M, K, N, seed = 2, 8200, 4100, 8190, 3
+    ctx = S.Context(n, P61, S.deal_alpha(P61, n, seed), seed)
+    X = ctx.spdz_deal_secret(seed, ARR_MX, S.ShareTensor.empty(n, 1, M * K))
+    Y = ctx.spdz_deal_secret(seed, ARR_MX + 1, S.ShareTensor.empty(n, 1, K * N))
+    T = ctx.spdz_deal_matrix_triple(seed, ARR_MX + 2, M, K, N, S.TripleTensor.empty_matrix(n, M, K, N))
+    out = []
+    for variant in (1, 0):
+        print(f"case panels variant={variant}", flush=True)
+        Z = S.ShareTensor.empty(n, 1, M * N)
+        ctx.spdz_matmul_triple(M, K, N, X, Y, T, Z, variant=variant)
+        assert ctx.spdz_mac_check()[0]
+        out.append(Z)
+    assert torch.equal(out[0].val, out[1].val) and torch.equal(out[0].mac, out[1].mac)
+    ctx.close()
