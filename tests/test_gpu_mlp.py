@@ -66,3 +66,35 @@ def test_training_fits_a_known_function():
     var = float(np.var(T))
     assert loss[-1] < 0.05 * var, (loss[-1], var)
     assert loss[-1] < loss[0]
+
+
+@pytest.mark.parametrize("B", [3, 4, 5, 16, 17, 63, 64, 65, 129, 16389])
+def test_batch_edges_match_reference(B):
+    """Batches at the edges of a wave's samples, a block's chunk, and several chunks per block; gradients of
+    long batches are sums of B terms of either sign, held to sqrt(B) roundings of their absolute sum."""
+    from paper_2512_11112_amd import spdz as S
+    W, X = data(B, B)
+    dY = np.random.default_rng(B + 1).standard_normal((B, 2)).astype(np.float32)
+    Wd, Xd = torch.from_numpy(W).cuda(), torch.from_numpy(X).cuda()
+    Y, A = S.mlp_forward(Wd, Xd, acts=True)
+    assert torch.equal(Y, S.mlp_forward(Wd, Xd))
+    Yr, acts = M.forward(W.astype(np.float64), X.astype(np.float64))
+    assert np.allclose(Y.cpu().numpy(), Yr, rtol=RTOL, atol=ATOL * max(1.0, np.abs(Yr).max()))
+    for k in range(3):
+        assert np.allclose(A[k].cpu().numpy(), acts[k], rtol=RTOL, atol=ATOL * max(1.0, np.abs(acts[k]).max()))
+    got = S.mlp_backward(Wd, Xd, A, torch.from_numpy(dY).cuda())
+    assert torch.equal(got, S.mlp_backward(Wd, Xd, A, torch.from_numpy(dY).cuda()))
+    # the device's own activations decide the ReLU masks, as they do on the device
+    own = [A[k].cpu().numpy().astype(np.float64) for k in range(3)]
+    g = M.backward(W.astype(np.float64), X.astype(np.float64), own, dY.astype(np.float64))
+    mag = M.backward(np.abs(W).astype(np.float64), np.abs(X).astype(np.float64), own, np.abs(dY).astype(np.float64))
+    assert np.all(np.abs(got.cpu().numpy() - g) <= 2.0 ** -24 * (200 + 4 * np.sqrt(B)) * mag + 1e-30)
+
+
+@pytest.mark.parametrize("B", [65536, 65537])
+def test_prediction_batches_agree(B):
+    """Outputs alone switch kernels above 65536 samples; the sums run in the same order in both."""
+    from paper_2512_11112_amd import spdz as S
+    W, X = data(B, B)
+    Wd, Xd = torch.from_numpy(W).cuda(), torch.from_numpy(X).cuda()
+    assert torch.equal(S.mlp_forward(Wd, Xd), S.mlp_forward(Wd, Xd, acts=True)[0])
