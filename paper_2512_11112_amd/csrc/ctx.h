@@ -56,7 +56,7 @@ struct spdz_ctx {
   spdz::u64 *h_sigma = nullptr;
   spdz::u64 *d_sigma = nullptr; // device address of h_sigma
   spdz::u64 fin_seq = 0;        // finalisations launched
-  unsigned *d_count = nullptr;  // blocks finished of the fused Beaver kernel (zero between launches)
+  unsigned *d_count = nullptr;  // blocks finished of a kernel whose last block finalises (zero between launches)
   // MAC-check sums contributed by ops that ran on the CPU back end ([0] = A, [1 + i] = G_i), canonical
   spdz::u64 host_acc[spdz::MAX_PARTIES + 1][2] = {};
   int grid_mult = 0;            // blocks per CU for streaming kernels (0 = from occupancy)
@@ -180,7 +180,6 @@ spdz_status launch_fused(spdz_ctx *c, const FusedIns *ins, int nins, int nslots,
 
 spdz_status launch_pubop(spdz_ctx *c, int mode, const spdz_shares *x, const u64 *v, int64_t vwidth,
                          spdz_shares *out);
-spdz_status launch_reduce_finalize(spdz_ctx *c, int grid, spdz_shares *out);
 spdz_status launch_maccheck_finalize(spdz_ctx *c);
 spdz_status launch_deal_secret(spdz_ctx *c, u64 seed, u64 array_id, const u64 *values, spdz_shares *out,
                                u64 *values_out);

@@ -165,28 +165,34 @@ __global__ __launch_bounds__(BLOCK) void k_pubop(const PubArgs<F, N> A) {
 }
 
 // --------------------------------------------------------------------------
-// ReduceAdd: per-block partials, then one-block finalisation
+// ReduceAdd: per-block partials, summed by the last block to finish (a device-scope count, reset for
+// the next launch), as in the fused Beaver kernel
 // --------------------------------------------------------------------------
 template <class F, int N>
-__global__ __launch_bounds__(BLOCK) void k_reduce(SV x, int64_t W, u64 *red) {
+__global__ __launch_bounds__(BLOCK) void k_reduce(SV x, int64_t W, u64 *red, SV out, unsigned *count) {
   using E = typename F::E;
   E s[2 * N];
 #pragma unroll
   for (int k = 0; k < 2 * N; k++) s[k] = F::zero();
-  for (int64_t e = (int64_t)blockIdx.x * BLOCK + threadIdx.x; e < W; e += (int64_t)gridDim.x * BLOCK) {
+  // EL elements a step, all requested before any is added
+  constexpr int EL = 2 * N * F::L <= 8 ? 4 : 2;
+  const int64_t stride = (int64_t)gridDim.x * BLOCK;
+  for (int64_t e = (int64_t)blockIdx.x * BLOCK + threadIdx.x; e < W; e += EL * stride) {
+    E v[EL][2 * N];
 #pragma unroll
-    for (int i = 0; i < N; i++) {
-      s[i] = F::add(s[i], F::load(x.val + i * x.ps, x.ls, e));
-      s[N + i] = F::add(s[N + i], F::load(x.mac + i * x.ps, x.ls, e));
-    }
+    for (int u = 0; u < EL; u++)
+#pragma unroll
+      for (int k = 0; k < 2 * N; k++) {
+        const bool in = e + u * stride < W;
+        v[u][k] = in ? F::load((k < N ? x.val : x.mac) + k % N * x.ps, x.ls, e + u * stride) : F::zero();
+      }
+#pragma unroll
+    for (int u = 0; u < EL; u++)
+#pragma unroll
+      for (int k = 0; k < 2 * N; k++) s[k] = F::add(s[k], v[u][k]);
   }
-  block_add_to_slot<F, 2 * N>(s, red + (size_t)blockIdx.x * 2 * N * F::L);
-}
-
-// sums slots [0, nslots) of red, writes the width-1 result to out, clears the slots
-template <class F, int N>
-__global__ __launch_bounds__(BLOCK) void k_reduce_finalize(u64 *red, int nslots, SV out) {
-  reduce_finalize_block<F, N>(red, nslots, out, nullptr, 0, 0, nullptr);
+  block_store_slot<F, 2 * N>(s, red + (size_t)blockIdx.x * 2 * N * F::L);
+  if (last_block(count)) reduce_finalize_block<F, N>(red, gridDim.x, out, nullptr, 0, 0, nullptr);
 }
 
 // --------------------------------------------------------------------------
@@ -201,30 +207,26 @@ struct FinArgs {
   u64 seq;
 };
 
-template <class F, int N>
-__global__ __launch_bounds__(BLOCK) void k_mac_finalize(const FinArgs<F, N> A) {
-  using E = typename F::E;
-  E s[N + 1];
-#pragma unroll
-  for (int k = 0; k <= N; k++) s[k] = F::zero();
-  for (int b = threadIdx.x; b < A.nslots; b += BLOCK) {
-    u64 *p = A.acc + (size_t)b * (N + 1) * F::L;
-#pragma unroll
-    for (int k = 0; k <= N; k++) {
-      s[k] = F::add(s[k], F::from_words(p + k * F::L));
-#pragma unroll
-      for (int l = 0; l < F::L; l++) p[k * F::L + l] = 0;
-    }
-  }
-  // totals of the device slots: [0] = sum r a, [1 + i] = sum r gamma_i, stored to pinned host
-  // memory, then the check's sequence number, which the host polls
-  E t = block_sum<F, N + 1>(s);
+// One block, bound by a round trip to the slots and one to the host; TH threads: 1024 where 256 would need
+// more than one round of requests each, else 256 (a larger block starts later: 2.9 against 3.7 us for 256
+// slots).  With fences for its stores it took 3.2 us for 256 slots and the host saw them later.
+template <class F, int N, int TH>
+__global__ __launch_bounds__(TH) void k_mac_finalize(const FinArgs<F, N> A) {
+  // totals of the device slots: [0] = sum r a, [1 + i] = sum r gamma_i, stored to pinned host memory
+  // (past the caches), and once they have arrived the check's sequence number, which the host polls;
+  // then the slots are cleared
+  const typename F::E t = slots_sum<F, N + 1, TH, false>(A.acc, A.nslots);
   if (threadIdx.x <= N) {
-    F::to_words(t, A.sigma + threadIdx.x * F::L);
-    __threadfence_system();
+    u64 w[F::L];
+    F::to_words(t, w);
+#pragma unroll
+    for (int l = 0; l < F::L; l++)
+      __hip_atomic_store(A.sigma + threadIdx.x * F::L + l, w[l], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   }
   __syncthreads();
-  if (threadIdx.x == 0) __hip_atomic_store(A.flag, A.seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+  if (threadIdx.x == 0) __hip_atomic_store(A.flag, A.seq, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+  for (int i = threadIdx.x; i < A.nslots * (N + 1) * F::L; i += TH) A.acc[i] = 0;
 }
 
 // --------------------------------------------------------------------------
@@ -592,20 +594,11 @@ spdz_status launch_reduce(spdz_ctx *c, const spdz_shares *x, spdz_shares *out) {
   return visit(c, [&](auto f, auto nn) -> spdz_status {
     using F = decltype(f);
     constexpr int N = decltype(nn)::value;
-    int g = grid_for(c, (const void *)k_reduce<F, N>, x->len);
+    // two blocks per CU: each counts itself on one word at its end (2048 blocks: 20 us of counting)
+    int g = grid_for(c, (const void *)k_reduce<F, N>, x->len, BLOCK, BLOCK, 2);
     KTimer tm(c, "reduce");
-    hipLaunchKernelGGL((k_reduce<F, N>), dim3(g), dim3(BLOCK), 0, c->stream, sv_of(x), x->len, c->d_red);
-    spdz_status st = hip_status(hipGetLastError());
-    if (st != SPDZ_OK) return st;
-    return launch_reduce_finalize(c, g, out);
-  });
-}
-
-spdz_status launch_reduce_finalize(spdz_ctx *c, int grid, spdz_shares *out) {
-  return visit(c, [&](auto f, auto nn) -> spdz_status {
-    using F = decltype(f);
-    constexpr int N = decltype(nn)::value;
-    hipLaunchKernelGGL((k_reduce_finalize<F, N>), dim3(1), dim3(BLOCK), 0, c->stream, c->d_red, grid, sv_of(out));
+    hipLaunchKernelGGL((k_reduce<F, N>), dim3(g), dim3(BLOCK), 0, c->stream, sv_of(x), x->len, c->d_red, sv_of(out),
+                       c->d_count);
     return hip_status(hipGetLastError());
   });
 }
@@ -620,7 +613,10 @@ spdz_status launch_maccheck_finalize(spdz_ctx *c) {
     A.sigma = c->d_sigma;
     A.flag = c->d_sigma + (MAX_PARTIES + 1) * 2;
     A.seq = ++c->fin_seq;
-    hipLaunchKernelGGL((k_mac_finalize<F, N>), dim3(1), dim3(BLOCK), 0, c->stream, A);
+    if (A.nslots * (N + 1) <= 8 * BLOCK)
+      hipLaunchKernelGGL((k_mac_finalize<F, N, BLOCK>), dim3(1), dim3(BLOCK), 0, c->stream, A);
+    else
+      hipLaunchKernelGGL((k_mac_finalize<F, N, 1024>), dim3(1), dim3(1024), 0, c->stream, A);
     return hip_status(hipGetLastError());
   });
 }

@@ -114,6 +114,25 @@ def test_open_linear_reduce(p, n, W):
     assert ok and ok_d and sig_d == ints_of_sigma(sig)
 
 
+@pytest.mark.parametrize("p,n,W", [(P61, 3, 131072), (P61, 3, 131073), (P127, 2, 131071), (P127, 8, 600), (P61, 8, 1),
+                                   (P127, 2, 400001), (P_PAPER, 5, 300007)])
+def test_reduce_and_check_slot_counts(p, n, W):
+    """ReduceAdd and the MAC check over few and many block slots (3 parties: 512 and 513 slots are the two
+    sides of the check's block size), twice in a row: slots and the count of blocks start anew."""
+    D = deal_elementwise(p, n, W, 3)
+    f = D.f
+    ctx = make_ctx(D, 3)
+    xd, yd = share_to_dev(D.x), share_to_dev(D.y)
+    for epoch, (sh, shd) in enumerate(((D.x, xd), (D.y, yd))):
+        eq_shares(ctx.spdz_reduce_add(shd), f.reduce_add(sh), "s")
+        log = F.MacLog(f, n, 3, epoch)
+        log.add(f.open(sh.val), sh.mac)
+        ok, sig = log.check(D.alpha)
+        assert np.array_equal(host(ctx.spdz_open(shd)), f.open(sh.val))
+        ok_d, sig_d = ctx.spdz_mac_check()
+        assert ok and ok_d and sig_d == ints_of_sigma(sig)
+
+
 def test_linear_aliasing_output():
     """spdz_linear allows out to alias a term: x <- 5 x + y."""
     D = deal_elementwise(P127, 3, 5001, 3)
