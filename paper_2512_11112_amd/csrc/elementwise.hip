@@ -180,16 +180,17 @@ __global__ __launch_bounds__(BLOCK) void k_reduce(SV x, int64_t W, u64 *red, SV 
   for (int64_t e = (int64_t)blockIdx.x * BLOCK + threadIdx.x; e < W; e += EL * stride) {
     E v[EL][2 * N];
 #pragma unroll
-    for (int u = 0; u < EL; u++)
+    for (int u = 0; u < EL; u++) {
+      const int64_t at = min(e + u * stride, W - 1);  // (past the end the last element, not added)
 #pragma unroll
-      for (int k = 0; k < 2 * N; k++) {
-        const bool in = e + u * stride < W;
-        v[u][k] = in ? F::load((k < N ? x.val : x.mac) + k % N * x.ps, x.ls, e + u * stride) : F::zero();
-      }
+      for (int k = 0; k < 2 * N; k++) v[u][k] = F::load((k < N ? x.val : x.mac) + k % N * x.ps, x.ls, at);
+    }
 #pragma unroll
-    for (int u = 0; u < EL; u++)
+    for (int u = 0; u < EL; u++) {
+      if (e + u * stride >= W) break;
 #pragma unroll
       for (int k = 0; k < 2 * N; k++) s[k] = F::add(s[k], v[u][k]);
+    }
   }
   block_store_slot<F, 2 * N>(s, red + (size_t)blockIdx.x * 2 * N * F::L);
   if (last_block(count)) reduce_finalize_block<F, N>(red, gridDim.x, out, nullptr, 0, 0, nullptr);
@@ -594,8 +595,10 @@ spdz_status launch_reduce(spdz_ctx *c, const spdz_shares *x, spdz_shares *out) {
   return visit(c, [&](auto f, auto nn) -> spdz_status {
     using F = decltype(f);
     constexpr int N = decltype(nn)::value;
-    // two blocks per CU: each counts itself on one word at its end (2048 blocks: 20 us of counting)
-    int g = grid_for(c, (const void *)k_reduce<F, N>, x->len, BLOCK, BLOCK, 2);
+    // three blocks per CU: each counts itself on one word at its end (2048 blocks: 20 us of counting), and two
+    // do not keep the memory busy (2^61 - 1, 2 parties, 2^24 elements: 95 us, three 83, four 84; 1000003
+    // elements over 2^127 - 1: 20, 23 and 25 us, a second launch to sum 2048 slots 27)
+    int g = grid_for(c, (const void *)k_reduce<F, N>, x->len, BLOCK, BLOCK, 3);
     KTimer tm(c, "reduce");
     hipLaunchKernelGGL((k_reduce<F, N>), dim3(g), dim3(BLOCK), 0, c->stream, sv_of(x), x->len, c->d_red, sv_of(out),
                        c->d_count);
