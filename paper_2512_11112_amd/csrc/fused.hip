@@ -150,6 +150,159 @@ __global__ __launch_bounds__(BLOCK) void k_fused(const FusedArgs<F, N> A) {
   block_add_to_slot<F, N + 1>(mc, A.acc + (size_t)blockIdx.x * (N + 1) * L);
 }
 
+// --------------------------------------------------------------------------
+// The same list for few elements, where one element's chain of round trips and instructions is what a run
+// waits for.  A lane takes one of the 2 N residues of an element (LANES per element), so the parties' and
+// MAC shares' arithmetic runs side by side and only d and e are summed across lanes; every word the list
+// reads, operands and triples, is requested up front straight into LDS, one round trip for the whole
+// list.  LDS: [slot, then operand in list order][words of a residue][thread], each thread its own column.
+// --------------------------------------------------------------------------
+// the byte fields of an instruction from one 8-byte word, which the scalar unit can load (bytes and
+// half-words it cannot: each would be a vector load's round trip on the list's way)
+struct FusedOp {
+  int kind, dst, a, b, flags;
+};
+__device__ __forceinline__ FusedOp fused_op(const FusedIns &I) {
+  u64 w;
+  __builtin_memcpy(&w, &I, 8);
+  return FusedOp{(int)(w & 255), (int)(w >> 8 & 255), (int)(w >> 16 & 255), (int)(w >> 24 & 255), (int)(w >> 32 & 255)};
+}
+
+// buffers an instruction reads through p0, p1, p2 (public operands apart)
+__host__ __device__ __forceinline__ int fused_operands(int kind, int flags) {
+  return kind == FK_BEAVER ? 3 : kind == FK_LOADS ? flags : kind == FK_LOAD ? 1 : 0;
+}
+
+// lanes per element: a power of two of at least 2 n
+__host__ __device__ constexpr int narrow_lanes(int n) { return n <= 2 ? 4 : n <= 4 ? 8 : 16; }
+
+struct NarrowOps {
+  const u64 *base[3 * FUSED_MAX_INS];  // the operands' buffers in list order
+  int n, nslots;
+};
+
+// sum of v over aligned groups of R lanes (R = 4, 8, 16), in every lane of the group
+template <class F, int R>
+__device__ __forceinline__ typename F::E group_sum(typename F::E v) {
+  auto step = [&](auto ctrl) {
+    u32 w[F::WORDS32];
+#pragma unroll
+    for (int k = 0; k < F::WORDS32; k++)
+      w[k] = (u32)__builtin_amdgcn_update_dpp(0, (int)F::word32(v, k), decltype(ctrl)::value, 15, 15, false);
+    v = F::add(v, F::from32(w));
+  };
+  step(std::integral_constant<int, 0xB1>{});                      // quad_perm [1, 0, 3, 2]
+  step(std::integral_constant<int, 0x4E>{});                      // quad_perm [2, 3, 0, 1]
+  if constexpr (R >= 8) step(std::integral_constant<int, 0x141>{});   // row_half_mirror: the other quad of 8
+  if constexpr (R >= 16) step(std::integral_constant<int, 0x140>{});  // row_mirror: the other half of 16
+  return v;
+}
+
+template <class F, int N>
+__global__ __launch_bounds__(BLOCK) void k_fused_narrow(const FusedArgs<F, N> A, const NarrowOps O) {
+  using E = typename F::E;
+  using Wd = typename F::Wide;
+  constexpr int L = F::L, D = F::WORDS32, R = narrow_lanes(N), EPB = BLOCK / R;
+  extern __shared__ u32 lds32[];
+  const int t = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(t >> 6), r = t & (R - 1);
+  const int64_t W = A.W, e0 = (int64_t)blockIdx.x * EPB + t / R, e = min(e0, W - 1);
+  const bool live = e0 < W && r < 2 * N;   // (other lanes follow along on words in bounds)
+  const int k = r < 2 * N ? r : 0;         // residue: value share of party k, or MAC share of party k - N
+  const bool mac = k >= N;
+  const int64_t at_k = (int64_t)k * L * W + e;
+  for (int o = 0; o < O.n; o++) {
+    const u64 *src = O.base[o] + at_k;
+#pragma unroll
+    for (int d = 0; d < D; d++)
+      __builtin_amdgcn_global_load_lds((const u32 *)(src + (d >> 1) * W) + (d & 1),
+                                       (__attribute__((address_space(3))) void *)(lds32 + ((O.nslots + o) * D + d) * BLOCK + wave * 64),
+                                       4, 0, 0);
+  }
+  // the block's MAC-check slot (its own: no other block of the launch touches it)
+  u64 *slot = A.acc + (size_t)blockIdx.x * (N + 1) * L;
+  const E prev = t < N + 1 ? F::from_words(slot + t * L) : F::zero();
+  E alpha = F::zero();
+#pragma unroll
+  for (int i = 0; i < N; i++)
+    if (k == N + i) alpha = A.alpha[i];
+  auto get = [&](int op) -> E {
+    u32 w[D];
+#pragma unroll
+    for (int d = 0; d < D; d++) w[d] = lds32[(op * D + d) * BLOCK + t];
+    return F::from32(w);
+  };
+  auto put = [&](int op, E x) {
+    x = F::canon(x);
+#pragma unroll
+    for (int d = 0; d < D; d++) lds32[(op * D + d) * BLOCK + t] = F::word32(x, d);
+  };
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // a wave reads only what it requested itself
+  E mc = F::zero();  // residue 0: sum r a; MAC share of party i: sum r gamma_i
+  for (int q = 0, at = O.nslots; q < A.nins; q++) {
+    const FusedIns &I = A.ins[q];
+    const FusedOp op = fused_op(I);
+    const int no = fused_operands(op.kind, op.flags);
+    if (op.kind == FK_LOAD || op.kind == FK_LOADS) {
+      for (int o = 0; o < no; o++) put(o == 0 ? op.dst : o == 1 ? op.a : op.b, get(at + o));
+      at += no;
+      continue;
+    }
+    const E x = get(op.a);
+    E out;
+    if (op.kind == FK_BEAVER) {
+      const E y = get(op.b), a = get(at), b = get(at + 1), c = get(at + 2);
+      const E rd = uniform_elem<F>(A.coef_state, (u64)(I.j + e));
+      const E re = uniform_elem<F>(A.coef_state, (u64)(I.j + W + e));
+      const E dx = F::sub(x, a), dy = F::sub(y, b);
+      const bool value = r < N;
+      const E d = group_sum<F, R>(value ? dx : F::zero()), ee = group_sum<F, R>(value ? dy : F::zero());
+      const E de = F::mul(d, ee);
+      Wd w = F::wzero();
+      F::wadd(w, c);
+      F::wmac(w, d, b);
+      F::wmac(w, ee, a);
+      // party 0's value share takes d e, a MAC share alpha_i d e
+      if (mac) F::wmac(w, alpha, de);
+      else if (k == 0) F::wadd(w, de);
+      out = F::wreduce(w);
+      Wd g = F::wzero();
+      F::wmac(g, rd, mac ? dx : d);
+      F::wmac(g, re, mac ? dy : ee);
+      mc = F::add(mc, F::wreduce(g));
+    } else if (op.kind == FK_LIN) {
+      const E y = get(op.b);
+      out = (op.flags & FF_SUB) ? F::sub(x, y) : F::add(x, y);
+    } else {  // public operand [L][W] or a scalar [L][1]
+      const bool vec = op.flags & FF_PUB_VEC;
+      const E v = F::load(I.p0, vec ? W : 1, vec ? e : 0);
+      if (op.kind == FK_PUBMUL) {
+        out = F::mul(x, v);
+      } else {  // (-)secret (+/-) public: party 0 adds to its value, party i adds alpha_i v to its MAC
+        const E pv = (op.flags & FF_NEG_P) ? F::sub(F::zero(), v) : v;
+        out = (op.flags & FF_NEG_A) ? F::sub(F::zero(), x) : x;
+        if (mac) out = F::add(out, F::mul(alpha, pv));
+        else if (k == 0) out = F::add(out, pv);
+      }
+    }
+    put(op.dst, out);
+    if ((op.flags & FF_STORE) && live) F::store(I.out + (int64_t)k * L * W, W, e, out);
+    at += no;
+  }
+  // the MAC-check sums of residue 0 and the MAC shares: over the wave's elements, then over the waves
+  if (!live) mc = F::zero();
+#pragma unroll
+  for (int off = 32; off >= R; off >>= 1) mc = F::add(mc, shfl_xor_e<F>(mc, off));
+  __shared__ E sh[WAVES][N + 1];
+  if ((t & 63) < 2 * N && (k == 0 || mac)) sh[wave][k == 0 ? 0 : 1 + k - N] = mc;
+  __syncthreads();
+  if (t < N + 1) {
+    E s = prev;
+#pragma unroll
+    for (int w = 0; w < WAVES; w++) s = F::add(s, sh[w][t]);
+    F::to_words(s, slot + t * L);
+  }
+}
+
 spdz_status launch_fused(spdz_ctx *c, const FusedIns *ins, int nins, int nslots, int64_t W) {
   if (nins < 1 || nins > FUSED_MAX_INS || nslots < 1 || nslots > fused_max_slots(c->n, c->L, c->fid) || W < 1)
     return SPDZ_E_INVAL;
@@ -165,6 +318,26 @@ spdz_status launch_fused(spdz_ctx *c, const FusedIns *ins, int nins, int nslots,
     alpha_of<F, N>(c, A.alpha);
     A.coef_state = coef_state(c);
     A.acc = c->d_acc;
+    // narrow: at most four blocks per CU (of BLOCK / LANES elements), and everything the list reads in LDS.
+    // A loop of three products and two additions, us per trip, narrow / wide: 2^32 - 5, 2 parties, width 64
+    // 7.0 / 9.0, 4096 7.5 / 13.1, 65536 (four blocks) 12.6 / 14.2, 131072 18.6 / 16.7; 2^61 - 1, 3 parties,
+    // width 1000 9.0 / 17.1, 32768 (four) 14.8 / 18.5, 65536 23.9 / 19.4.
+    NarrowOps O;
+    O.n = 0;
+    O.nslots = nslots;
+    for (int q = 0; q < nins; q++) {
+      const u64 *p[3] = {ins[q].p0, ins[q].p1, ins[q].p2};
+      for (int o = 0; o < fused_operands(ins[q].kind, ins[q].flags); o++) O.base[O.n++] = p[o];
+    }
+    constexpr int EPB = BLOCK / narrow_lanes(N);
+    const int64_t narrow_lds = (int64_t)(nslots + O.n) * F::WORDS32 * BLOCK * 4, blocks = (W + EPB - 1) / EPB;
+    if (blocks <= 4 * c->num_cus && blocks <= MAX_SLOTS && narrow_lds <= FUSED_LDS_BYTES) {
+      KTimer tm(c, "fused");
+      hipLaunchKernelGGL((k_fused_narrow<F, N>), dim3((unsigned)blocks), dim3(BLOCK), (size_t)narrow_lds, c->stream, A, O);
+      spdz_status s = hip_status(hipGetLastError());
+      if (s == SPDZ_OK && blocks > c->slots) c->slots = (int)blocks;
+      return s;
+    }
     const size_t lds = (size_t)nslots * 2 * N * F::L * fused_word_bytes(c->fid) * BLOCK;
     const void *k = (const void *)k_fused<F, N>;
     const int g = grid_for(c, k, W);

@@ -366,3 +366,23 @@ def test_random_c_functions_on_the_runtime():
             ctx.close()
         ran += 1
     assert ran >= 30
+
+
+@pytest.mark.parametrize("p,n,W", [(P_PAPER, 2, 65536), (P_PAPER, 2, 65537), (P61, 3, 32768), (P61, 3, 32769),
+                                   (P61, 4, 33), (P61, 5, 17), (P61, 8, 1), (P_PAPER, 8, 300), (P_PAPER, 2, 63)])
+def test_narrow_and_wide_runs_match_node_by_node(p, n, W):
+    """Fused runs on both sides of the width at which they change kernels, and at partial blocks of each number
+    of lanes per element: outputs and sigma as with every node its own kernel."""
+    from paper_2512_11112_amd import spdz as S
+    got = []
+    for fuse in (True, False):
+        ctx = S.Context(n, p, S.deal_alpha(p, n, 5), 5)
+        prog = S.Program(ctx, P.loop_program(W, 3), fuse=fuse)
+        ok, sigma, _ = prog.run(5)
+        assert ok
+        acc = prog.output(6)
+        got.append((sigma, acc.val, acc.mac, prog.output(15)))
+        prog.close()
+        ctx.close()
+    assert got[0][0] == got[1][0]
+    assert all(torch.equal(a, b) for a, b in zip(got[0][1:], got[1][1:]))
