@@ -15,6 +15,32 @@ __device__ __forceinline__ typename F::E shfl_xor_e(typename F::E a, int mask) {
   return F::from32(w);
 }
 
+// sum of v over aligned groups of R lanes (R = 4, 8, 16), in every lane of the group: lane exchanges
+// within a row of 16 lanes are operand modifiers, without the LDS's round trip that a shuffle takes
+template <class F, int R>
+__device__ __forceinline__ typename F::E group_sum(typename F::E v) {
+  auto step = [&](auto ctrl) {
+    u32 w[F::WORDS32];
+#pragma unroll
+    for (int k = 0; k < F::WORDS32; k++)
+      w[k] = (u32)__builtin_amdgcn_update_dpp(0, (int)F::word32(v, k), decltype(ctrl)::value, 15, 15, false);
+    v = F::add(v, F::from32(w));
+  };
+  step(std::integral_constant<int, 0xB1>{});                      // quad_perm [1, 0, 3, 2]
+  step(std::integral_constant<int, 0x4E>{});                      // quad_perm [2, 3, 0, 1]
+  if constexpr (R >= 8) step(std::integral_constant<int, 0x141>{});   // row_half_mirror: the other quad of 8
+  if constexpr (R >= 16) step(std::integral_constant<int, 0x140>{});  // row_mirror: the other half of 16
+  return v;
+}
+
+// sum of v over the wave, in every lane
+template <class F>
+__device__ __forceinline__ typename F::E wave_sum(typename F::E v) {
+  v = group_sum<F, 16>(v);
+  v = F::add(v, shfl_xor_e<F>(v, 16));
+  return F::add(v, shfl_xor_e<F>(v, 32));
+}
+
 // Sum v[k] over the block; the total of component k is returned in thread k
 // (k < K), other threads get zero.  Contains __syncthreads(): call from every
 // thread of the block.
@@ -23,10 +49,7 @@ __device__ typename F::E block_sum(typename F::E (&v)[K]) {
   using E = typename F::E;
   __shared__ E sh[WAVES][K];
 #pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) {
-#pragma unroll
-    for (int k = 0; k < K; k++) v[k] = F::add(v[k], shfl_xor_e<F>(v[k], off));
-  }
+  for (int k = 0; k < K; k++) v[k] = wave_sum<F>(v[k]);
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   __syncthreads();  // sh may be in use by a previous call
   if (lane == 0) {

@@ -181,23 +181,6 @@ struct NarrowOps {
   int n, nslots;
 };
 
-// sum of v over aligned groups of R lanes (R = 4, 8, 16), in every lane of the group
-template <class F, int R>
-__device__ __forceinline__ typename F::E group_sum(typename F::E v) {
-  auto step = [&](auto ctrl) {
-    u32 w[F::WORDS32];
-#pragma unroll
-    for (int k = 0; k < F::WORDS32; k++)
-      w[k] = (u32)__builtin_amdgcn_update_dpp(0, (int)F::word32(v, k), decltype(ctrl)::value, 15, 15, false);
-    v = F::add(v, F::from32(w));
-  };
-  step(std::integral_constant<int, 0xB1>{});                      // quad_perm [1, 0, 3, 2]
-  step(std::integral_constant<int, 0x4E>{});                      // quad_perm [2, 3, 0, 1]
-  if constexpr (R >= 8) step(std::integral_constant<int, 0x141>{});   // row_half_mirror: the other quad of 8
-  if constexpr (R >= 16) step(std::integral_constant<int, 0x140>{});  // row_mirror: the other half of 16
-  return v;
-}
-
 template <class F, int N>
 __global__ __launch_bounds__(BLOCK) void k_fused_narrow(const FusedArgs<F, N> A, const NarrowOps O) {
   using E = typename F::E;

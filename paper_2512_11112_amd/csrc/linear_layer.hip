@@ -142,13 +142,6 @@ __global__ __launch_bounds__(BLOCK) void k_ll_open_e(const LayerArgs<F, N, Wt> A
   block_add_to_slot<F, N + 1>(mc, A.acc + (size_t)blockIdx.x * (N + 1) * F::L);
 }
 
-template <class F>
-__device__ __forceinline__ typename F::E wave_sum(typename F::E v) {
-#pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) v = F::add(v, shfl_xor_e<F>(v, off));
-  return v;
-}
-
 // one block per group of up to R consecutive rows of one tile (grid-stride over the groups),
 // the rows' elements strided by the block size, V consecutive elements per lane (V = 4 needs
 // din, the party strides and the base addresses to be multiples of 4 words): each element's
