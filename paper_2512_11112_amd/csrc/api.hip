@@ -164,7 +164,7 @@ spdz_status spdz_ctx_create(spdz_ctx **out, int n_parties, const uint64_t *p_lim
       hipHostMalloc((void **)&c->h_sigma, (size_t)(2 * (MAX_PARTIES + 1) + 1) * 8,
                     hipHostMallocMapped | hipHostMallocCoherent) != hipSuccess ||
       hipHostGetDevicePointer((void **)&c->d_sigma, c->h_sigma, 0) != hipSuccess ||
-      hipMalloc((void **)&c->d_count, 256) != hipSuccess ||
+      hipMalloc((void **)&c->d_count, (1 + COUNT_GROUPS) * COUNT_STRIDE * sizeof(unsigned)) != hipSuccess ||
       hipMalloc((void **)&c->d_bad, 256) != hipSuccess ||
       hipHostMalloc((void **)&c->h_bad, sizeof(uint32_t), hipHostMallocDefault) != hipSuccess) {
     spdz_ctx_destroy(c);
@@ -172,7 +172,7 @@ spdz_status spdz_ctx_create(spdz_ctx **out, int n_parties, const uint64_t *p_lim
   }
   memset(c->h_sigma, 0, (size_t)(2 * (MAX_PARTIES + 1) + 1) * 8);
   if (hipMemset(c->d_acc, 0, acc_words * 8) != hipSuccess || hipMemset(c->d_red, 0, red_words * 8) != hipSuccess ||
-      hipMemset(c->d_count, 0, 256) != hipSuccess ||
+      hipMemset(c->d_count, 0, (1 + COUNT_GROUPS) * COUNT_STRIDE * sizeof(unsigned)) != hipSuccess ||
       hipDeviceSynchronize() != hipSuccess) {
     spdz_ctx_destroy(c);
     return SPDZ_E_HIP;

@@ -19,6 +19,7 @@ constexpr int MIN_PARTIES = 2;
 constexpr int BLOCK = 256;          // threads per block of the element-wise kernels
 constexpr int WAVES = BLOCK / 64;   // wave64
 constexpr int MAX_SLOTS = 4096;     // per-block accumulator slots (upper bound on grid size)
+constexpr int COUNT_GROUPS = 32, COUNT_STRIDE = 32;  // block counts of a kernel whose last block finalises
 constexpr int64_t MAX_MFMA_K = 8191; // the matrix engine's moduli cover sums of 2K <= 16382 products
 
 // fields of a context
@@ -56,7 +57,7 @@ struct spdz_ctx {
   spdz::u64 *h_sigma = nullptr;
   spdz::u64 *d_sigma = nullptr; // device address of h_sigma
   spdz::u64 fin_seq = 0;        // finalisations launched
-  unsigned *d_count = nullptr;  // blocks finished of a kernel whose last block finalises (zero between launches)
+  unsigned *d_count = nullptr;  // [1 + COUNT_GROUPS][COUNT_STRIDE] blocks finished (last_block; zero between launches)
   // MAC-check sums contributed by ops that ran on the CPU back end ([0] = A, [1 + i] = G_i), canonical
   spdz::u64 host_acc[spdz::MAX_PARTIES + 1][2] = {};
   int grid_mult = 0;            // blocks per CU for streaming kernels (0 = from occupancy)

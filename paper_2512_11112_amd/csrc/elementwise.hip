@@ -595,9 +595,9 @@ spdz_status launch_reduce(spdz_ctx *c, const spdz_shares *x, spdz_shares *out) {
   return visit(c, [&](auto f, auto nn) -> spdz_status {
     using F = decltype(f);
     constexpr int N = decltype(nn)::value;
-    // three blocks per CU: each counts itself on one word at its end (2048 blocks: 20 us of counting), and two
-    // do not keep the memory busy (2^61 - 1, 2 parties, 2^24 elements: 95 us, three 83, four 84; 1000003
-    // elements over 2^127 - 1: 20, 23 and 25 us, a second launch to sum 2048 slots 27)
+    // three blocks per CU: more have more slots to store, count and sum, and two do not keep the memory busy at
+    // large widths (2^61 - 1, 2 parties, 2^24 elements: two 95 us, three 78, six 88; 1000003 elements over
+    // 2^127 - 1: three 16.9, six 18.1, eight 19.1 us, a second launch to sum 2048 slots 27)
     int g = grid_for(c, (const void *)k_reduce<F, N>, x->len, BLOCK, BLOCK, 3);
     KTimer tm(c, "reduce");
     hipLaunchKernelGGL((k_reduce<F, N>), dim3(g), dim3(BLOCK), 0, c->stream, sv_of(x), x->len, c->d_red, sv_of(out),

@@ -133,6 +133,18 @@ def test_reduce_and_check_slot_counts(p, n, W):
         assert ok and ok_d and sig_d == ints_of_sigma(sig)
 
 
+@pytest.mark.parametrize("blocks", [1, 2, 31, 32, 33, 64, 65])
+def test_reduce_block_count_groups(blocks):
+    """ReduceAdd around the 32 groups its blocks count in (one element a thread: 256 a block), three times in a
+    row over the same counters."""
+    W = 256 * blocks - 3
+    D = deal_elementwise(P61, 2, W, 5)
+    f = D.f
+    ctx = make_ctx(D, 3)
+    for sh in (D.x, D.y, D.x):
+        eq_shares(ctx.spdz_reduce_add(share_to_dev(sh)), f.reduce_add(sh), "s")
+
+
 def test_linear_aliasing_output():
     """spdz_linear allows out to alias a term: x <- 5 x + y."""
     D = deal_elementwise(P127, 3, 5001, 3)
