@@ -15,6 +15,16 @@ __device__ __forceinline__ typename F::E shfl_xor_e(typename F::E a, int mask) {
   return F::from32(w);
 }
 
+// v of the lane's neighbour in its pair
+template <class F>
+__device__ __forceinline__ typename F::E lane_xor1(typename F::E v) {
+  u32 w[F::WORDS32];
+#pragma unroll
+  for (int k = 0; k < F::WORDS32; k++)
+    w[k] = (u32)__builtin_amdgcn_update_dpp(0, (int)F::word32(v, k), 0xB1, 15, 15, false);  // quad_perm [1, 0, 3, 2]
+  return F::from32(w);
+}
+
 // sum of v over aligned groups of R lanes (R = 4, 8, 16), in every lane of the group: lane exchanges
 // within a row of 16 lanes are operand modifiers, without the LDS's round trip that a shuffle takes
 template <class F, int R>

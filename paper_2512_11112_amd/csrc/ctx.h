@@ -166,17 +166,31 @@ spdz_status launch_reduce(spdz_ctx *c, const spdz_shares *x, spdz_shares *out);
 enum FusedKind : uint8_t { FK_LOAD = 0, FK_BEAVER = 1, FK_LIN = 2, FK_PUBADD = 3, FK_PUBMUL = 4, FK_LOADS = 5 };
 enum FusedFlag : uint8_t { FF_STORE = 1, FF_SUB = 2, FF_NEG_A = 4, FF_NEG_P = 8, FF_PUB_VEC = 16 };
 struct FusedIns {
-  uint8_t kind, dst, a, b, flags, pad[3];
+  uint8_t kind, dst, a, b, flags, reads, pad[2];  // reads: fused_operands (filled in by the launch)
   const u64 *p0, *p1, *p2;  // LOAD: node buffer; BEAVER: triple a, b, c buffers; PUB*: public [L][W or 1]
   u64 *out;                 // FF_STORE: node buffer the result is written to
   int64_t j;                // BEAVER: log index of d_0 (e_0 at j + W)
 };
-constexpr int FUSED_MAX_INS = 24;
-constexpr int FUSED_LDS_BYTES = 61440;  // dynamic LDS of one group launch
+constexpr int FUSED_GROUP_INS = 24;     // instructions of one group
+constexpr int FUSED_MAX_INS = 64;       // instructions of one launch (groups joined)
+constexpr int FUSED_LDS_BYTES = 61440;  // dynamic LDS of one launch, a thread an element
 // bytes of one LDS word of a slot: residues below 2^32 take 4, others 8 per limb
 inline int fused_word_bytes(int fid) { return fid == FID_32 ? 4 : 8; }
-inline int fused_max_slots(int n, int L, int fid) { return FUSED_LDS_BYTES / (2 * n * L * fused_word_bytes(fid) * BLOCK); }
-// runs the group over W elements; Beaver instructions add to the MAC-check slots
+constexpr int FUSED_MAX_SLOTS = 32;  // (over any field and number of parties)
+inline int fused_max_slots(int n, int L, int fid) {
+  const int most = FUSED_LDS_BYTES / (2 * n * L * fused_word_bytes(fid) * BLOCK);
+  return most < FUSED_MAX_SLOTS ? most : FUSED_MAX_SLOTS;
+}
+// slots a list over W elements may use (below 3: none, a product's operands and result do not fit)
+int fused_slots(const spdz_ctx *c, int64_t W);
+// whether a list of `nslots` slots that loads `operands` buffers can run over W elements, and, for groups
+// joined into one list, whether it keeps to the kernel of the width
+bool fused_runs(const spdz_ctx *c, int nslots, int operands, int64_t W, bool joined);
+// buffers an instruction reads through p0, p1, p2
+inline int fused_operands(int kind, int flags) {
+  return kind == FK_BEAVER ? 3 : kind == FK_LOADS ? flags : kind == FK_LIN ? 0 : 1;
+}
+// runs the list over W elements; Beaver instructions add to the MAC-check slots
 spdz_status launch_fused(spdz_ctx *c, const FusedIns *ins, int nins, int nslots, int64_t W);
 
 spdz_status launch_pubop(spdz_ctx *c, int mode, const spdz_shares *x, const u64 *v, int64_t vwidth,

@@ -386,3 +386,72 @@ def test_narrow_and_wide_runs_match_node_by_node(p, n, W):
         ctx.close()
     assert got[0][0] == got[1][0]
     assert all(torch.equal(a, b) for a, b in zip(got[0][1:], got[1][1:]))
+
+
+def joining_program(W, trips):
+    """A loop of two values carried in one fused run: every kind of instruction of a fused run, a public operand
+    of full width and of one element, a value read again in the next iteration, one read only after the loop."""
+    return f"""
+input 1 private {W} 0
+input 2 private {W} 1
+input 20 public {W} 7
+const 3 1 {trips}
+const 4 1 0
+const 5 1 1
+const 21 1 77
+output 6
+output 18
+output 14
+block 0
+br 1
+block 1
+6 = phi 1 0 9 2
+18 = phi 2 0 17 2
+7 = phi 4 0 10 2
+8 = lt 7 3
+cbr 8 2 3
+block 2
+11 = mul 6 2
+9 = add 11 1
+12 = sub 20 9
+13 = mul 12 21
+14 = sub 13 20
+15 = mul 14 9
+16 = add 15 21
+17 = sub 16 18
+10 = add 7 5
+br 1
+block 3
+ret
+"""
+
+
+@pytest.mark.parametrize("trips", [1, 7, 8, 25])  # 8 and more: several launches of joined runs
+@pytest.mark.parametrize("p,n,W", [(P_PAPER, 2, 1), (P_PAPER, 2, 32769), (P61, 2, 1000), (P61, 3, 16384), (P61, 3, 16385),
+                                   (P61, 8, 130), (P127, 2, 77), (P127, 2, 32769)])
+def test_joined_runs_match_node_by_node(p, n, W, trips):
+    """Iterations of a loop that share a launch, both kernels: outputs and sigma as with every node its own kernel,
+    and, at small sizes, the oracle's."""
+    from paper_2512_11112_amd import spdz as S
+    text, got = joining_program(W, trips), []
+    for fuse, ahead in ((True, True), (True, False), (False, True)):
+        ctx = S.Context(n, p, S.deal_alpha(p, n, 5), 5)
+        prog = S.Program(ctx, text, fuse=fuse)
+        if ahead:
+            prog.predeal(5, trips)
+        sigma = []
+        for _ in range(2):  # a second run starts anew (and a new epoch of the check)
+            ok, s, _ = prog.run(5)
+            assert ok
+            sigma.append(s)
+        outs = [prog.output(o) for o in (6, 18, 14)]
+        got.append((sigma, [t for o in outs for t in (o.val, o.mac)]))
+        prog.close()
+        if W * trips <= 2000:
+            ref = run_program(text, p, n, 5, 5)
+            assert sigma[0] == ints_of_sigma(ref["sigma"])
+            assert np.array_equal(host(outs[1].val), ref["outputs"][18].val)
+        ctx.close()
+    for g in got[:2]:
+        assert g[0] == got[2][0]
+        assert all(torch.equal(a, b) for a, b in zip(g[1], got[2][1]))
