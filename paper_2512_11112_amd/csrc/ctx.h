@@ -148,7 +148,8 @@ struct KTimer {
 // launchers (elementwise.hip)
 spdz_status launch_open(spdz_ctx *c, const spdz_shares *x, u64 *out_pub);
 // opens sum_i (x_i - sub_i) (the mask step of a Beaver product), logging it with MAC shares m(x)_i - m(sub)_i
-spdz_status launch_open_diff(spdz_ctx *c, const spdz_shares *x, const spdz_shares *sub, u64 *out_pub);
+spdz_status launch_open_diffs(spdz_ctx *c, const spdz_shares *x0, const spdz_shares *s0, u64 *out0,
+                              const spdz_shares *x1, const spdz_shares *s1, u64 *out1);
 // s (with w or alone: the fused kernel) = ReduceAdd(z), finalised by the kernel's last block, which
 // also opens it into s_pub (nullable)
 spdz_status launch_beaver(spdz_ctx *c, const spdz_shares *x, const spdz_shares *y, const spdz_triple *t,

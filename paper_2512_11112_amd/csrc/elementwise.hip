@@ -29,7 +29,6 @@ namespace spdz {
 template <class F, int N>
 struct OpenArgs {
   SV x;
-  SV sub;  // if sub.val != nullptr the opened value is sum_i (x_i - sub_i), MAC shares m(x)_i - m(sub)_i
   u64 *out;
   int64_t W;
   u64 coef_state;
@@ -48,16 +47,49 @@ __global__ __launch_bounds__(BLOCK) void k_open(const OpenArgs<F, N> a) {
     E m[N];
 #pragma unroll
     for (int i = 0; i < N; i++) {
-      E v = F::load(a.x.val + i * a.x.ps, a.x.ls, e);
       m[i] = F::load(a.x.mac + i * a.x.ps, a.x.ls, e);
-      if (a.sub.val) {
-        v = F::sub(v, F::load(a.sub.val + i * a.sub.ps, a.sub.ls, e));
-        m[i] = F::sub(m[i], F::load(a.sub.mac + i * a.sub.ps, a.sub.ls, e));
-      }
-      s = F::add(s, v);
+      s = F::add(s, F::load(a.x.val + i * a.x.ps, a.x.ls, e));
     }
     F::store(a.out, a.W, e, s);
     const E r = uniform_elem<F>(a.coef_state, (u64)(a.j0 + e));
+    mc[0] = F::add(mc[0], F::mul(r, s));
+#pragma unroll
+    for (int i = 0; i < N; i++) mc[1 + i] = F::add(mc[1 + i], F::mul(r, m[i]));
+  }
+  block_add_to_slot<F, N + 1>(mc, a.acc + (size_t)blockIdx.x * (N + 1) * F::L);
+}
+
+// x[0] - sub[0], then x[1] - sub[1], as one run of the log: the two opens of a matrix triple (small ones are
+// mostly launches, 8 us each).
+template <class F, int N>
+struct OpenDiffsArgs {
+  SV x[2], sub[2];
+  u64 *out[2];
+  int64_t W[2];
+  u64 coef_state;
+  int64_t j0;
+  u64 *acc;
+};
+
+template <class F, int N>
+__global__ __launch_bounds__(BLOCK) void k_open_diffs(const OpenDiffsArgs<F, N> a) {
+  using E = typename F::E;
+  E mc[N + 1];
+#pragma unroll
+  for (int k = 0; k <= N; k++) mc[k] = F::zero();
+  for (int64_t j = (int64_t)blockIdx.x * BLOCK + threadIdx.x; j < a.W[0] + a.W[1]; j += (int64_t)gridDim.x * BLOCK) {
+    const bool second = j >= a.W[0];
+    const SV x = second ? a.x[1] : a.x[0], sub = second ? a.sub[1] : a.sub[0];
+    const int64_t e = second ? j - a.W[0] : j;
+    E s = F::zero();
+    E m[N];
+#pragma unroll
+    for (int i = 0; i < N; i++) {
+      s = F::add(s, F::sub(F::load(x.val + i * x.ps, x.ls, e), F::load(sub.val + i * sub.ps, sub.ls, e)));
+      m[i] = F::sub(F::load(x.mac + i * x.ps, x.ls, e), F::load(sub.mac + i * sub.ps, sub.ls, e));
+    }
+    F::store(second ? a.out[1] : a.out[0], second ? a.W[1] : a.W[0], e, s);
+    const E r = uniform_elem<F>(a.coef_state, (u64)(a.j0 + j));
     mc[0] = F::add(mc[0], F::mul(r, s));
 #pragma unroll
     for (int i = 0; i < N; i++) mc[1 + i] = F::add(mc[1 + i], F::mul(r, m[i]));
@@ -503,16 +535,11 @@ spdz_status validate_result(spdz_ctx *c) {
 }
 
 spdz_status launch_open(spdz_ctx *c, const spdz_shares *x, u64 *out_pub) {
-  return launch_open_diff(c, x, nullptr, out_pub);
-}
-
-spdz_status launch_open_diff(spdz_ctx *c, const spdz_shares *x, const spdz_shares *sub, u64 *out_pub) {
   return visit(c, [&](auto f, auto nn) -> spdz_status {
     using F = decltype(f);
     constexpr int N = decltype(nn)::value;
     OpenArgs<F, N> a;
     a.x = sv_of(x);
-    a.sub = sub ? sv_of(sub) : SV{nullptr, nullptr, 0, 0};
     a.out = out_pub;
     a.W = x->len;
     a.coef_state = coef_state(c);
@@ -525,6 +552,27 @@ spdz_status launch_open_diff(spdz_ctx *c, const spdz_shares *x, const spdz_share
     spdz_status s = hip_status(hipGetLastError());
     if (s == SPDZ_OK) {
       c->log_count += x->len;
+      if (g > c->slots) c->slots = g;
+    }
+    return s;
+  });
+}
+
+// opens x0 - s0 into out0, then x1 - s1 into out1
+spdz_status launch_open_diffs(spdz_ctx *c, const spdz_shares *x0, const spdz_shares *s0, u64 *out0,
+                              const spdz_shares *x1, const spdz_shares *s1, u64 *out1) {
+  return visit(c, [&](auto f, auto nn) -> spdz_status {
+    using F = decltype(f);
+    constexpr int N = decltype(nn)::value;
+    const OpenDiffsArgs<F, N> a{{sv_of(x0), sv_of(x1)}, {sv_of(s0), sv_of(s1)}, {out0, out1},  {x0->len, x1->len},
+                                coef_state(c),          c->log_count,           c->d_acc};
+    const int64_t W = x0->len + x1->len;
+    const int g = grid_for(c, (const void *)k_open_diffs<F, N>, W);
+    KTimer tm(c, "open");
+    hipLaunchKernelGGL((k_open_diffs<F, N>), dim3(g), dim3(BLOCK), 0, c->stream, a);
+    spdz_status s = hip_status(hipGetLastError());
+    if (s == SPDZ_OK) {
+      c->log_count += W;
       if (g > c->slots) c->slots = g;
     }
     return s;

@@ -177,10 +177,11 @@ __global__ __launch_bounds__(256) void k_planes(const PlaneArgs A) {
       d[j] = rns::digits(v);
     }
     int8_t *out = S.out + t0 * step + (rb * A.ks + kb) * PB + c * 1024 + pr * 16;
+    rns::Digits next = B.digits[left][t0];
 #pragma unroll 1
     for (int t = t0; t < t1; t++) {
-      const int c0 = (int)B.c0[left][t], c1 = (int)B.c1[left][t], bias = (int)B.bias[t], neg = B.neg[t];
-      const float inv = B.inv[t];
+      const rns::Digits D = next;
+      next = B.digits[left][t + 1];
       u32 pk[4];
 #pragma unroll
       for (int q = 0; q < 4; q++) {
@@ -188,9 +189,9 @@ __global__ __launch_bounds__(256) void k_planes(const PlaneArgs A) {
 #pragma unroll
         for (int i = 0; i < 4; i++) {
           const int j = 4 * q + i;
-          const int s = __builtin_amdgcn_sdot4((int)d[j], c0,
-                                               __builtin_amdgcn_sdot4((int)(d[j] >> 32), c1, bias, false), false);
-          r[i] = rns::round_mod((u32)s, inv, neg);
+          const int s = __builtin_amdgcn_sdot4((int)d[j], D.c0,
+                                               __builtin_amdgcn_sdot4((int)(d[j] >> 32), D.c1, D.bias, false), false);
+          r[i] = rns::round_mod((u32)s, D.inv, D.neg);
         }
         pk[q] = pack4(r[0], r[1], r[2], r[3]);
       }
@@ -662,8 +663,7 @@ spdz_status launch_matmul_triple(spdz_ctx *c, int64_t M, int64_t K, int64_t N, c
   auto open = [&](char *ws) -> spdz_status {
     if (!E) E = (u64 *)ws;
     if (!Fm) Fm = (u64 *)(ws + e_bytes);
-    SPDZ_RET(launch_open_diff(c, X, &T->a, E));
-    return launch_open_diff(c, Y, &T->b, Fm);
+    return launch_open_diffs(c, X, &T->a, E, Y, &T->b, Fm);
   };
   auto a_of = [&](int i, bool mac) { return (mac ? T->a.mac : T->a.val) + i * T->a.party_stride; };
   auto b_of = [&](int i, bool mac) { return (mac ? T->b.mac : T->b.val) + i * T->b.party_stride; };

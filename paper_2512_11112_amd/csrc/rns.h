@@ -31,18 +31,23 @@ constexpr int FRAC = 23;  // u_t / m_t is summed in units of 2^-23
 constexpr u64 P = (1ull << 61) - 1;
 constexpr u64 mulp(u64 a, u64 b) { return (u64)((u128)a * b % P); }
 
+// Residue of a balanced value mod m_t: the dot product of its signed base-256 digits with the powers of 256
+// mod m_t, balanced (c0 low digits, c1 high), and what round_mod takes.  One record, one scalar load.
+struct alignas(32) Digits {
+  int c0, c1;
+  int bias;  // bits of the float 2^23 + b with b = 2^18 to 2^18 + 255 and m_t | 2^23 + b: an integer
+             // |s| < 2^18 added to them is the float 2^23 + b + s
+  int neg;   // -m_t
+  float inv;
+};
+
 // constants of one choice of T (17 or 18)
 struct Tables {
-  // residue of a balanced value: the dot product of its signed base-256 digits with the powers of 256
-  // mod m_t, balanced; index [left][t] (left: times (M / m_t)^-1)
-  u32 c0[2][TMAX], c1[2][TMAX];
+  Digits digits[2][TMAX + 1];  // [left][t] (left: the powers times (M / m_t)^-1); one more is read ahead
   float inv[TMAX];     // 1 / m_t
   int neg[TMAX];       // -m_t
   int c14[TMAX];       // 2^14 mod m_t, balanced
-  // bits of the float 2^23 + b with b = 2^18 to 2^18 + 255 and m_t | 2^23 + b: an integer |s| < 2^18 added
-  // to them is the float 2^23 + b + s
-  u32 bias[TMAX];
-  // the same for |s| < 2^21, the low 14 bits zero
+  // bits of the float 2^23 + b, b a multiple of 2^14 from 130 2^14 on, m_t | 2^23 + b: as Digits::bias for |s| < 2^21
   u32 bias14[TMAX];
   // (M / m_t) mod p: byte j of the weights of moduli 4 g .. 4 g + 3, packed
   u32 w[5][8];
@@ -71,13 +76,16 @@ constexpr Tables make_tables(int T) {
     for (int left = 0; left < 2; left++) {
       const int k = left ? inverse : 1;
       int pw = 1;  // 256^j mod m
+      u32 c[2] = {0, 0};
       for (int j = 0; j < 8; j++) {
-        const int c = pw * k % m;
-        const u32 byte = (u32)(c > 127 ? c - m : c) & 255;  // m even only for 256: 128 stays -128
-        if (j < 4) r.c0[left][t] |= byte << (8 * j);
-        else r.c1[left][t] |= byte << (8 * (j - 4));
+        const int v = pw * k % m;
+        const u32 byte = (u32)(v > 127 ? v - m : v) & 255;  // m even only for 256: 128 stays -128
+        if (j < 4) c[0] |= byte << (8 * j);
+        else c[1] |= byte << (8 * (j - 4));
         pw = pw * 256 % m;
       }
+      r.digits[left][t].c0 = (int)c[0];
+      r.digits[left][t].c1 = (int)c[1];
     }
     r.inv[t] = 1.0f / (float)m;
     r.neg[t] = -m;
@@ -86,7 +94,12 @@ constexpr Tables make_tables(int T) {
     u32 b = 1u << 18, b14 = 130u << 14;
     while (((1u << 23) + b) % (u32)m != 0) b++;
     while (((1u << 23) + b14) % (u32)m != 0) b14 += 1u << 14;
-    r.bias[t] = 0x4B000000u + b;
+    for (int left = 0; left < 2; left++) {
+      Digits &d = r.digits[left][t];
+      d.bias = (int)(0x4B000000u + b);
+      d.neg = r.neg[t];
+      d.inv = r.inv[t];
+    }
     r.bias14[t] = 0x4B000000u + b14;
     const u32 f = (u32)(((2u << FRAC) / (u32)m + 1) / 2);
     for (int j = 0; j < 8; j++) r.w[t / 4][j] |= (u32)((w >> (8 * j)) & 255) << (8 * (t % 4));
