@@ -156,7 +156,8 @@ __global__ __launch_bounds__(256) void k_mlp_predict(const float *__restrict__ W
 // over the chunks of CHUNK samples this block takes, into out + blockIdx.x NPARAM.  Per chunk the 8
 // waves form the deltas of the pre-activations they need (lane k sums column k of the weights), the
 // block then its group's outer products, a thread eight of them, samples in ascending order.
-// A block keeps the deltas on chip: 11 us at batch 32 (58 at 8192), where deltas by one thread per
+// A block keeps the deltas on chip: 10 us at batch 32 (58 at 8192; 12 with the samples' LDS reads one at a
+// time), where deltas by one thread per
 // sample (43-47 us) and products by one thread per parameter (11; 2300 at 8192) met in memory.
 constexpr int CHUNK = 64;
 __global__ __launch_bounds__(512) void k_mlp_backward(const float *__restrict__ W, const float *__restrict__ X,
@@ -216,6 +217,7 @@ __global__ __launch_bounds__(512) void k_mlp_backward(const float *__restrict__ 
     __syncthreads();
     if (group > 0) {  // 2 rows x 4 columns a thread; a bias in each of the first 64
       const int j = t >> 4 << 1, k = (t & 15) << 2;
+#pragma unroll 4
       for (int b = 0; b < n; b++) {
         const float2 d = *reinterpret_cast<const float2 *>(D + b * HID + j);
         const float4 v = *reinterpret_cast<const float4 *>(in + b * HID + k);
@@ -229,14 +231,21 @@ __global__ __launch_bounds__(512) void k_mlp_backward(const float *__restrict__ 
         g[7] = fmaf(d.y, v.w, g[7]);
       }
       if (t < HID)
+#pragma unroll 8
         for (int b = 0; b < n; b++) ga += D[b * HID + t];
     } else {  // first layer: 448 weights and 64 biases; head: 128 weights and 2 biases
       const int j = t / IN, k = t % IN;
-      for (int b = 0; b < n; b++)
-        ga = t < HID * IN ? fmaf(D[b * HID + j], xs[b * IN + k], ga) : ga + D[b * HID + t - HID * IN];
+      if (t < HID * IN)
+#pragma unroll 8
+        for (int b = 0; b < n; b++) ga = fmaf(D[b * HID + j], xs[b * IN + k], ga);
+      else
+#pragma unroll 8
+        for (int b = 0; b < n; b++) ga += D[b * HID + t - HID * IN];
       if (t < OUT * HID)
+#pragma unroll 8
         for (int b = 0; b < n; b++) gb = fmaf(dy[b * OUT + t / HID], in[b * HID + t % HID], gb);
       else if (t < OUT * HID + OUT)
+#pragma unroll 8
         for (int b = 0; b < n; b++) gb += dy[b * OUT + t - OUT * HID];
     }
     __syncthreads();  // the chunk's rows are reused
