@@ -72,6 +72,7 @@ struct PNode {
   int64_t log_static = 0, opens = 0;  // position of its openings inside a block entry, values opened
   bool heavy = false, device = false;  // issued before light nodes; runs on the device
   bool dev_use = false;  // a public value that a device kernel (or the output call) reads
+  bool host_use = false; // an open whose words the host reads
   int group = -1;        // fused element-wise group (one kernel for the group's nodes)
   // buffers
   spdz_shares sh{};      // secret value: device [n][L][width] (values, MACs)
@@ -483,6 +484,13 @@ spdz_status infer(spdz_prog *g) {
   }
   for (int o : g->outputs)
     if (!N[o].secret) N[o].dev_use = true;
+  for (int b : g->block_order) {
+    const PBlock &B = g->blocks[b];
+    if (B.term == 2) N[B.cond].host_use = true;
+    for (int id : B.lines)
+      for (int u : N[id].users)
+        if (!N[u].device || N[u].op == OP_LOAD) N[id].host_use = true;
+  }
   // a layer's W that is an input is packed once, when it is dealt (packed layers, p = 2^32 - 5)
   if (g->c->fid == FID_32)
     for (int b : g->block_order)
@@ -1438,9 +1446,9 @@ spdz_status issue(spdz_prog *g, PNode &n) {
       PNode &a = N[n.args[0]];
       c->log_count = n.log_off;
       st = launch_open(c, &a.sh, n.dpub);
-      if (st == SPDZ_OK)
+      if (st == SPDZ_OK && n.host_use)
         st = hip_status(hipMemcpyAsync(n.hpub, n.dpub, (size_t)L * n.width * 8, hipMemcpyDeviceToHost, c->stream));
-      n.await_host = true;
+      n.await_host = n.host_use;
       g->launches++;
       break;
     }
@@ -1594,7 +1602,7 @@ spdz_status deal_inputs(spdz_prog *g) {
         }
         return SPDZ_OK;
       });
-      SPDZ_RET(upload(g, n));
+      if (n.dev_use) SPDZ_RET(upload(g, n));
     }
   }
   return stream_sync(g);
