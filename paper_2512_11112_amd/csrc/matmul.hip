@@ -528,8 +528,9 @@ struct RnsPlan {
   size_t lbytes, rbytes, sbytes;
 };
 
-// largest workspace taken without trying panels
-constexpr size_t RNS_WS = (size_t)8 << 30;
+// largest workspace taken without trying panels, and the least: allocations up to it take 14 us, beyond 92
+// (and 310 to free), and a small product after the dealer's smaller still does not allocate again
+constexpr size_t RNS_WS = (size_t)8 << 30, RNS_WS_MIN = (size_t)64 << 20;
 
 RnsPlan rns_plan(const RnsProblem &P, int T, int tm, int tn, int64_t pm, int64_t pn) {
   const int64_t kp = up(P.K, 64);
@@ -620,7 +621,8 @@ spdz_status rns_run(spdz_ctx *c, RnsProblem &P, size_t head, int bpc, Open &&ope
     const size_t need = head + plan.lbytes + plan.rbytes + plan.sbytes;
     const bool last = pm == tm && pn == tn;
     if (need <= RNS_WS + head || last) {
-      const spdz_status s = ensure_ws(c, need);
+      spdz_status s = c->ws_bytes >= need ? SPDZ_OK : ensure_ws(c, std::max(need, RNS_WS_MIN));
+      if (s == SPDZ_E_NOMEM && need < RNS_WS_MIN) s = ensure_ws(c, need);
       if (s == SPDZ_OK) {
         char *ws = (char *)c->ws;
         SPDZ_RET(open(ws));
