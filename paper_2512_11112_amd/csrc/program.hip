@@ -1751,14 +1751,28 @@ spdz_status spdz_prog_output(spdz_prog *g, int node, spdz_shares *out_shares, ui
   spdz_ctx *c = g->c;
   if (n.secret) {
     if (!out_shares || out_shares->len != n.width) return SPDZ_E_SHAPE;
-    for (int i = 0; i < c->n; i++)
-      for (int l = 0; l < c->L; l++) {
-        const size_t so = ((size_t)i * c->L + l) * n.width;
-        const size_t dof = (size_t)i * out_shares->party_stride + (size_t)l * out_shares->limb_stride;
-        if (hipMemcpyAsync(out_shares->val + dof, n.sh.val + so, n.width * 8, hipMemcpyDeviceToDevice, c->stream) != hipSuccess ||
-            hipMemcpyAsync(out_shares->mac + dof, n.sh.mac + so, n.width * 8, hipMemcpyDeviceToDevice, c->stream) != hipSuccess)
-          return SPDZ_E_HIP;
+    // the planes of values and of MAC shares: all in one copy each where they are equally spaced (a copy is
+    // about 9 us of the stream), else the parties' planes of a limb, else one by one
+    const int64_t ps = out_shares->party_stride, ls = out_shares->limb_stride, w = n.width;
+    const bool all = c->L == 1 || ps == c->L * ls, rows = all || ps >= w;
+    const int64_t pitch = all && c->L > 1 ? ls : ps;
+    const int per = all ? c->n * c->L : c->n, copies = all ? 1 : c->L;  // rows of a copy, copies
+    for (int h = 0; h < 2; h++) {
+      u64 *dst = h ? out_shares->mac : out_shares->val;
+      const u64 *src = h ? n.sh.mac : n.sh.val;
+      if (rows && pitch >= w) {
+        for (int l = 0; l < copies; l++)
+          if (hipMemcpy2DAsync(dst + l * ls, pitch * 8, src + l * w, (all ? 1 : c->L) * w * 8, w * 8, per,
+                               hipMemcpyDeviceToDevice, c->stream) != hipSuccess)
+            return SPDZ_E_HIP;
+        continue;
       }
+      for (int i = 0; i < c->n; i++)
+        for (int l = 0; l < c->L; l++)
+          if (hipMemcpyAsync(dst + i * ps + l * ls, src + ((size_t)i * c->L + l) * w, w * 8, hipMemcpyDeviceToDevice,
+                             c->stream) != hipSuccess)
+            return SPDZ_E_HIP;
+    }
   } else {
     if (!out_pub) return SPDZ_E_INVAL;
     if (hipMemcpyAsync(out_pub, n.dpub, (size_t)c->L * n.width * 8, hipMemcpyDeviceToDevice, c->stream) != hipSuccess)

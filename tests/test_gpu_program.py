@@ -455,3 +455,32 @@ def test_joined_runs_match_node_by_node(p, n, W, trips):
     for g in got[:2]:
         assert g[0] == got[2][0]
         assert all(torch.equal(a, b) for a, b in zip(g[1], got[2][1]))
+
+
+@pytest.mark.parametrize("p,n", [(P61, 3), (P127, 2)])
+@pytest.mark.parametrize("layout", ["dense", "padded", "parties_apart", "limbs_apart"])
+def test_output_into_strided_shares(p, n, layout):
+    """spdz_prog_output into every spacing of planes: one copy, one per limb, one per plane."""
+    import ctypes
+    from paper_2512_11112_amd import spdz as S
+    W, L = 301, 2 if p == P127 else 1
+    ps, ls = {"dense": (L * W, W), "padded": (L * (W + 5), W + 5), "parties_apart": (L * W + 9, W + 2 if L > 1 else W),
+              "limbs_apart": (W, n * W)}[layout]
+    ctx = ctx_for(p, n, 4, 5)
+    prog = S.Program(ctx, P.loop_program(W, 2), fuse=True)
+    assert prog.run(4)[0]
+    ref = prog.output(6)
+    size = n * ps + L * ls
+    val, mac = (torch.zeros(size, dtype=torch.int64, device="cuda") for _ in range(2))
+    d = S.Shares(val=val.data_ptr(), mac=mac.data_ptr(), len=W, party_stride=ps, limb_stride=ls)
+    assert S.lib().spdz_prog_output(prog._h, 6, ctypes.byref(d), None) == 0
+    for got, want in ((host(val), host(ref.val)), (host(mac), host(ref.mac))):
+        want, left = want.reshape(n, L, W), got.copy()
+        for i in range(n):
+            for l in range(L):
+                at = i * ps + l * ls
+                assert np.array_equal(got[at:at + W], want[i, l])
+                left[at:at + W] = 0
+        assert not left.any()
+    prog.close()
+    ctx.close()
