@@ -174,7 +174,7 @@ __global__ __launch_bounds__(BLOCK) void k_fused(const FusedArgs<F, N> A) {
 // MAC shares' arithmetic runs side by side and only d and e are summed across lanes.  The list itself comes
 // into LDS in one round trip (walked through the scalar cache, each line of the kernel arguments was one,
 // 0.45 us an instruction), then every word it reads, operands, triples and public operands, straight into LDS
-// in a second.  After that an addition takes 0.18 us and a product 0.65 (2^32 - 5, 2 parties; 0.9 at 3 parties
+// in a second.  After that an addition takes 0.18 us and a product 0.65 (2^32 - 5, 2 parties; 0.8 at 3 parties
 // over 2^61 - 1, 2.3 over 2^127 - 1): a wave's own chain of dependent instructions.
 // LDS: [slot, then operand in list order][words of a residue][thread], each thread its own column.
 // --------------------------------------------------------------------------
@@ -252,6 +252,12 @@ __global__ __launch_bounds__(BLOCK) void k_fused_narrow(const NarrowArgs<F, N> A
   };
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // a wave reads only what it requested itself
   E mc = F::zero();  // residue 0: sum r a; MAC share of party i: sum r gamma_i
+  constexpr int TERMS = [] {  // products of two residues that Wide holds
+    if constexpr (L == 1) return F::WIDE_TERMS;
+    else return 2;
+  }();
+  Wd g = F::wzero();
+  int terms = 0;  // Beaver products in g, two terms each
   const u32 *fields = reinterpret_cast<const u32 *>(list);
   constexpr int STEP = sizeof(NarrowIns) / 4;
   u32 f0 = fields[0], f1 = fields[1];
@@ -279,10 +285,13 @@ __global__ __launch_bounds__(BLOCK) void k_fused_narrow(const NarrowArgs<F, N> A
       F::wmac(w, ee, a);
       F::wmac(w, alpha, de);
       out = F::wreduce(w);
-      Wd g = F::wzero();
       F::wmac(g, rd, mac ? dx : d);
       F::wmac(g, re, mac ? dy : ee);
-      mc = F::add(mc, F::wreduce(g));
+      if (++terms == TERMS / 2) {
+        mc = F::add(mc, F::wreduce(g));
+        g = F::wzero();
+        terms = 0;
+      }
     } else if (kind == FK_LIN) {
       out = F::add(x, (flags & FF_SUB) ? F::sub(F::zero(), y) : y);
     } else if (kind == FK_LOAD || kind == FK_LOADS) {
@@ -304,6 +313,7 @@ __global__ __launch_bounds__(BLOCK) void k_fused_narrow(const NarrowArgs<F, N> A
     if ((flags & FF_STORE) && live) F::store(I.out + (int64_t)k * L * W, W, e, out);
     at += reads;
   }
+  mc = F::add(mc, F::wreduce(g));
   // the MAC-check sums of residue 0 and the MAC shares: over the wave's elements, then over the waves
   if (!live) mc = F::zero();
 #pragma unroll
