@@ -277,8 +277,8 @@ spdz_status spdz_linear_layer32(spdz_ctx *ctx, int64_t dout, int64_t din, int64_
  *              Chinese remainder theorem (K <= 8191, else SPDZ_E_SHAPE),
  *         -1 = library choice (MFMA).
  * Grows a library-owned workspace on first use (for the MFMA variant 18 ((2 n + 1) (M K + K N) +
- * 2 n M N) bytes with the sizes rounded up to whole tiles, at most 8 GiB while one tile of each
- * side fits: larger products run in panels); the call is asynchronous. */
+ * 2 n M N) bytes with the sizes rounded up to whole tiles, at least 64 MB where it can be had, at most
+ * 8 GiB while one tile of each side fits: larger products run in panels); the call is asynchronous. */
 spdz_status spdz_matmul_triple(spdz_ctx *ctx, int64_t M, int64_t K, int64_t N, const spdz_shares *X,
                                const spdz_shares *Y, const spdz_triple *T, spdz_shares *Z,
                                uint64_t *E_pub, uint64_t *F_pub, int variant);

@@ -1,8 +1,8 @@
-// Sustained int8 MFMA rate of this GPU for the exact-GEMM accumulation pattern:
-// 4 waves per block, each wave issuing 128 v_mfma_i32_32x32x32_i8 per step into
-// 15 shift-class accumulators (8 x 8 digit pairs, two 32-deep halves), operands held
-// in registers (no memory traffic at all).  Run once with random operand bytes (the
-// digits of uniformly random residues look like this) and once with small structured
+// Sustained int8 MFMA rate of this GPU: 4 waves per block, each wave issuing 128
+// v_mfma_i32_32x32x32_i8 per step into 15 accumulators (sums of 8 x 8 operand pairs by
+// their index sum, two 32-deep halves), operands held in registers (no memory traffic at
+// all).  Run once with random operand bytes (residues of uniformly random values modulo
+// byte-sized numbers look like this) and once with small structured
 // operands: the gap between the two is the clock the chip can hold at its power limit
 // when the matrix cores switch random data, i.e. the practical ceiling for the GEMM.
 //
