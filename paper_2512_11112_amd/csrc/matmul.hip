@@ -23,6 +23,7 @@
 #include <algorithm>
 
 #include "ctx.h"
+#include "panels.h"
 #include "rns.h"
 
 namespace spdz {
@@ -497,8 +498,6 @@ spdz_status ensure_ws(spdz_ctx *c, size_t bytes) {
 
 namespace {
 
-int64_t up(int64_t x, int64_t m) { return (x + m - 1) / m * m; }
-
 spdz_status valu_gemm(spdz_ctx *c, const GemmArgs &G, int nout) {
   dim3 grid((unsigned)((G.N + TILE - 1) / TILE), (unsigned)((G.M + TILE - 1) / TILE), (unsigned)nout);
   KTimer tm(c, "matmul_valu");
@@ -619,7 +618,7 @@ spdz_status rns_run(spdz_ctx *c, RnsProblem &P, size_t head, int bpc, Open &&ope
   for (;;) {
     const RnsPlan plan = rns_plan(P, T, tm, tn, pm, pn);
     const size_t need = head + plan.lbytes + plan.rbytes + plan.sbytes;
-    const bool last = pm == tm && pn == tn;
+    const bool last = pm <= tm && pn <= tn;
     if (need <= RNS_WS + head || last) {
       spdz_status s = c->ws_bytes >= need ? SPDZ_OK : ensure_ws(c, std::max(need, RNS_WS_MIN));
       if (s == SPDZ_E_NOMEM && need < RNS_WS_MIN) s = ensure_ws(c, need);
@@ -630,8 +629,7 @@ spdz_status rns_run(spdz_ctx *c, RnsProblem &P, size_t head, int bpc, Open &&ope
       }
       if (s != SPDZ_E_NOMEM || last) return s;
     }
-    if (pm >= pn) pm = up((pm + 1) / 2, tm);
-    else pn = up((pn + 1) / 2, tn);
+    smaller_panel(pm, pn, tm, tn);
   }
 }
 
