@@ -101,7 +101,10 @@ const char *spdz_status_str(spdz_status s);
  * share alpha_i (Sec. II-A).  check_seed keys the public coefficients of the MAC
  * check.  hip_stream is a hipStream_t (NULL = the default stream) on which every
  * call of this context is enqueued; the device is the current one.  Synchronous.
- * *out receives a library-owned context (free with spdz_ctx_destroy). */
+ * *out receives a library-owned context (free with spdz_ctx_destroy).  The environment
+ * variable SPDZ_WORKSPACE_LIMIT (bytes; read here) bounds the workspace that the
+ * context's matrix products and layers take: products that need more run in smaller
+ * panels, and a call that cannot returns SPDZ_E_NOMEM. */
 spdz_status spdz_ctx_create(spdz_ctx **out, int n_parties, const uint64_t *p_limbs, int n_limbs,
                             const uint64_t *alpha_shares, uint64_t check_seed, void *hip_stream);
 

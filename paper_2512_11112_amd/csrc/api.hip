@@ -146,6 +146,7 @@ spdz_status spdz_ctx_create(spdz_ctx **out, int n_parties, const uint64_t *p_lim
   c->stream = (hipStream_t)hip_stream;
   if (const char *g = getenv("SPDZ_GRID_PER_CU")) c->grid_mult = atoi(g);
   if (const char *v = getenv("SPDZ_VALIDATE")) c->validate = atoi(v) != 0;
+  if (const char *w = getenv("SPDZ_WORKSPACE_LIMIT")) c->ws_limit = strtoull(w, nullptr, 10);
   hipDeviceProp_t prop;
   if (hipGetDevice(&c->device) != hipSuccess || hipGetDeviceProperties(&prop, c->device) != hipSuccess) {
     delete c;
@@ -159,14 +160,14 @@ spdz_status spdz_ctx_create(spdz_ctx **out, int n_parties, const uint64_t *p_lim
   }
   const size_t acc_words = (size_t)MAX_SLOTS * (n_parties + 1) * n_limbs;
   const size_t red_words = (size_t)MAX_SLOTS * 2 * n_parties * n_limbs;
-  if (hipMalloc((void **)&c->d_acc, acc_words * 8) != hipSuccess ||
-      hipMalloc((void **)&c->d_red, red_words * 8) != hipSuccess ||
-      hipHostMalloc((void **)&c->h_sigma, (size_t)(2 * (MAX_PARTIES + 1) + 1) * 8,
+  if (dev_alloc(&c->d_acc, acc_words * 8) != hipSuccess ||
+      dev_alloc(&c->d_red, red_words * 8) != hipSuccess ||
+      host_alloc(&c->h_sigma, (size_t)(2 * (MAX_PARTIES + 1) + 1) * 8,
                     hipHostMallocMapped | hipHostMallocCoherent) != hipSuccess ||
       hipHostGetDevicePointer((void **)&c->d_sigma, c->h_sigma, 0) != hipSuccess ||
-      hipMalloc((void **)&c->d_count, (1 + COUNT_GROUPS) * COUNT_STRIDE * sizeof(unsigned)) != hipSuccess ||
-      hipMalloc((void **)&c->d_bad, 256) != hipSuccess ||
-      hipHostMalloc((void **)&c->h_bad, sizeof(uint32_t), hipHostMallocDefault) != hipSuccess) {
+      dev_alloc(&c->d_count, (1 + COUNT_GROUPS) * COUNT_STRIDE * sizeof(unsigned)) != hipSuccess ||
+      dev_alloc(&c->d_bad, 256) != hipSuccess ||
+      host_alloc(&c->h_bad, sizeof(uint32_t), hipHostMallocDefault) != hipSuccess) {
     spdz_ctx_destroy(c);
     return SPDZ_E_NOMEM;
   }
@@ -549,7 +550,7 @@ spdz_status spdz_deal_matvec_triple(spdz_ctx *c, uint64_t seed, uint64_t array_i
   // public A, B and C live in a temporary buffer
   u64 *tmp = nullptr;
   const size_t words = (size_t)(dout * din) + (size_t)(n_tiles * din) + (size_t)dout;
-  if (hipMalloc((void **)&tmp, words * 8) != hipSuccess) return SPDZ_E_NOMEM;
+  if (dev_alloc(&tmp, words * 8) != hipSuccess) return SPDZ_E_NOMEM;
   u64 *av = tmp, *bv = tmp + (size_t)(dout * din), *cv = bv + (size_t)(n_tiles * din);
   spdz_status s = launch_deal_secret(c, seed, array_id, nullptr, &t->a, av);
   if (s == SPDZ_OK) s = launch_deal_secret(c, seed, array_id + 1, nullptr, &t->b, bv);
@@ -573,7 +574,7 @@ spdz_status spdz_deal_matrix_triple(spdz_ctx *c, uint64_t seed, uint64_t array_i
   // the value streams of array_id and array_id + 1, C is shared with array_id + 2
   u64 *tmp = nullptr;
   const size_t words = (size_t)M * K + (size_t)K * N + (size_t)M * N;
-  if (hipMalloc((void **)&tmp, words * 8) != hipSuccess) return SPDZ_E_NOMEM;
+  if (dev_alloc(&tmp, words * 8) != hipSuccess) return SPDZ_E_NOMEM;
   u64 *av = tmp, *bv = tmp + (size_t)M * K, *cv = bv + (size_t)K * N;
   spdz_status s = launch_deal_secret(c, seed, array_id, nullptr, &t->a, av);
   if (s == SPDZ_OK) s = launch_deal_secret(c, seed, array_id + 1, nullptr, &t->b, bv);

@@ -68,6 +68,7 @@ struct spdz_ctx {
   // workspace of the matrix-triple product (residue planes, opened matrices), grown on demand
   void *ws = nullptr;
   size_t ws_bytes = 0;
+  size_t ws_limit = 0;          // largest workspace (0 = what the device has)
   // kernel timing (spdz_timing_enable): HIP events around each main kernel
   bool timing = false;
   struct Pending {
@@ -109,6 +110,21 @@ spdz_status visit(const spdz_ctx *c, Fn &&fn) {
 }
 
 inline spdz_status hip_status(hipError_t e) { return e == hipSuccess ? SPDZ_OK : SPDZ_E_HIP; }
+
+// The library's allocations.  A failed one is reported by its own status alone: left behind as the thread's
+// last error, which later successful calls do not replace, it would be taken for that of the next launch.
+inline hipError_t no_error(hipError_t e) {
+  if (e != hipSuccess) (void)hipGetLastError();
+  return e;
+}
+template <class T>
+hipError_t dev_alloc(T **p, size_t bytes) {
+  return no_error(hipMalloc((void **)p, bytes));
+}
+template <class T>
+hipError_t host_alloc(T **p, size_t bytes, unsigned flags) {
+  return no_error(hipHostMalloc((void **)p, bytes, flags));
+}
 
 #define SPDZ_RET(expr)                    \
   do {                                    \
@@ -216,7 +232,8 @@ spdz_status launch_matmul_triple(spdz_ctx *c, int64_t M, int64_t K, int64_t N, c
                                  const spdz_shares *Y, const spdz_triple *T, spdz_shares *Z, u64 *E_pub, u64 *F_pub,
                                  int variant);
 spdz_status launch_public_matmul(spdz_ctx *c, int64_t M, int64_t K, int64_t N, const u64 *A, const u64 *B, u64 *C);
-// grows the context workspace to at least `bytes` (waits for the stream before freeing the old one)
+// Grows the context workspace to at least `bytes` (waits for the stream before freeing the old one, which is
+// given up first only where both are not to be had together)
 spdz_status ensure_ws(spdz_ctx *c, size_t bytes);
 // linear_layer.hip
 // E_scratch: where the opened E_t go when E_pub is null (null: the context workspace, grown on demand)

@@ -425,12 +425,12 @@ spdz_status spdz_dag_create(spdz_ctx *c, int n_inputs, const int64_t *input_widt
   g->opened = jl;
   g->h_ops.resize(n_ops);
   for (int64_t k = 0; k < n_ops; k++) fill_dev_op(g, k, g->h_ops[k]);
-  bool ok = hipMalloc((void **)&g->nval, off * 8) == hipSuccess && hipMalloc((void **)&g->nmac, off * 8) == hipSuccess &&
-            hipMalloc((void **)&g->tval, std::max<int64_t>(toff, 1) * 8) == hipSuccess &&
-            hipMalloc((void **)&g->tmac, std::max<int64_t>(toff, 1) * 8) == hipSuccess &&
-            hipMalloc((void **)&g->d_ops, std::max<int64_t>(n_ops, 1) * sizeof(DagOpDev)) == hipSuccess &&
-            hipMalloc((void **)&g->d_list, std::max<int64_t>(n_ops, 1) * sizeof(int32_t)) == hipSuccess &&
-            hipMalloc((void **)&g->d_params, sizeof(DagParams)) == hipSuccess;
+  bool ok = dev_alloc(&g->nval, off * 8) == hipSuccess && dev_alloc(&g->nmac, off * 8) == hipSuccess &&
+            dev_alloc(&g->tval, std::max<int64_t>(toff, 1) * 8) == hipSuccess &&
+            dev_alloc(&g->tmac, std::max<int64_t>(toff, 1) * 8) == hipSuccess &&
+            dev_alloc(&g->d_ops, std::max<int64_t>(n_ops, 1) * sizeof(DagOpDev)) == hipSuccess &&
+            dev_alloc(&g->d_list, std::max<int64_t>(n_ops, 1) * sizeof(int32_t)) == hipSuccess &&
+            dev_alloc(&g->d_params, sizeof(DagParams)) == hipSuccess;
   if (!ok) {
     spdz_dag_destroy(g);
     return SPDZ_E_NOMEM;
@@ -649,7 +649,7 @@ static spdz_status upload_plan(spdz_dag *g, const GpuPlan &plan, DagOpDev *d_ops
     const int64_t want = std::max<int64_t>(ni, 2 * item_cap);
     d_item = nullptr;
     item_cap = 0;
-    if (hipMalloc((void **)&d_item, want * sizeof(int32_t)) != hipSuccess) return SPDZ_E_NOMEM;
+    if (dev_alloc(&d_item, want * sizeof(int32_t)) != hipSuccess) return SPDZ_E_NOMEM;
     item_cap = want;
   }
   if (ni > 0)
@@ -947,7 +947,7 @@ static spdz_status ensure_stage(spdz_dag *g, int b, int64_t words) {
   g->h_stage[b] = g->d_stage[b] = nullptr;
   g->stage_cap[b] = 0;
   const int64_t cap = std::max<int64_t>(words, 1 << 16);
-  if (hipHostMalloc((void **)&g->h_stage[b], (size_t)cap * 8, hipHostMallocMapped) != hipSuccess) return SPDZ_E_NOMEM;
+  if (host_alloc(&g->h_stage[b], (size_t)cap * 8, hipHostMallocMapped) != hipSuccess) return SPDZ_E_NOMEM;
   if (hipHostGetDevicePointer((void **)&g->d_stage[b], g->h_stage[b], 0) != hipSuccess) return SPDZ_E_HIP;
   g->stage_cap[b] = cap;
   return SPDZ_OK;
@@ -1055,7 +1055,7 @@ static spdz_status stage_triples(spdz_dag *g, const std::vector<uint8_t> &on_gpu
       if (g->d_xfer) (void)hipFree(g->d_xfer);
       g->d_xfer = nullptr;
       g->xfer_cap = 0;
-      if (hipMalloc(&g->d_xfer, bytes) != hipSuccess) return SPDZ_E_NOMEM;
+      if (dev_alloc(&g->d_xfer, bytes) != hipSuccess) return SPDZ_E_NOMEM;
       g->xfer_cap = (int64_t)bytes;
     }
     SPDZ_RET(hip_status(hipMemcpyAsync(g->d_xfer, segs.data(), bytes, hipMemcpyHostToDevice, g->stream)));
@@ -1113,8 +1113,8 @@ static spdz_status run_graph(spdz_dag *g) {
     g->gexec = nullptr;
     g->graph = nullptr;
     if (!g->d_ops_graph) {
-      if (hipMalloc((void **)&g->d_ops_graph, std::max<int64_t>(g->n_ops, 1) * sizeof(DagOpDev)) != hipSuccess ||
-          hipMalloc((void **)&g->d_list_graph, std::max<int64_t>(g->n_ops, 1) * sizeof(int32_t)) != hipSuccess)
+      if (dev_alloc(&g->d_ops_graph, std::max<int64_t>(g->n_ops, 1) * sizeof(DagOpDev)) != hipSuccess ||
+          dev_alloc(&g->d_list_graph, std::max<int64_t>(g->n_ops, 1) * sizeof(int32_t)) != hipSuccess)
         return SPDZ_E_NOMEM;
     }
     GpuPlan plan;
@@ -1229,7 +1229,7 @@ spdz_status spdz_dag_run(spdz_dag *g, int mode, int policy, double *wall_ms) {
         if (g->d_xfer) (void)hipFree(g->d_xfer);
         g->d_xfer = nullptr;
         g->xfer_cap = 0;
-        if (hipMalloc(&g->d_xfer, bytes) != hipSuccess) return SPDZ_E_NOMEM;
+        if (dev_alloc(&g->d_xfer, bytes) != hipSuccess) return SPDZ_E_NOMEM;
         g->xfer_cap = (int64_t)bytes;
       }
       SPDZ_RET(hip_status(hipMemcpyAsync(g->d_xfer, xp.segs.data(), bytes, hipMemcpyHostToDevice, g->stream)));
@@ -1344,7 +1344,7 @@ spdz_status spdz_dag_autotune(spdz_dag *g, int max_levels, int *tile_out, int *b
   SPDZ_RET(ensure_stream(g));
   SPDZ_RET(hip_status(hipStreamSynchronize(c->stream)));
   if (!g->tune_acc &&
-      hipMalloc((void **)&g->tune_acc, (size_t)MAX_SLOTS * (MAX_PARTIES + 1) * sizeof(u64)) != hipSuccess)
+      dev_alloc(&g->tune_acc, (size_t)MAX_SLOTS * (MAX_PARTIES + 1) * sizeof(u64)) != hipSuccess)
     return SPDZ_E_NOMEM;
   SPDZ_RET(set_params(g));
   const int tiles[] = {256, 512, 1024, 2048, 4096, 8192};
@@ -1423,8 +1423,8 @@ spdz_status dag_decide_learned(spdz_dag *g, std::vector<uint8_t> &on_gpu) {
   const int64_t B = g->n_ops;
   if (B == 0) return SPDZ_OK;
   if (!g->d_feat) {
-    if (hipMalloc((void **)&g->d_feat, (size_t)B * SPDZ_MLP_IN * sizeof(float)) != hipSuccess ||
-        hipMalloc((void **)&g->d_pred, (size_t)B * SPDZ_MLP_OUT * sizeof(float)) != hipSuccess)
+    if (dev_alloc(&g->d_feat, (size_t)B * SPDZ_MLP_IN * sizeof(float)) != hipSuccess ||
+        dev_alloc(&g->d_pred, (size_t)B * SPDZ_MLP_OUT * sizeof(float)) != hipSuccess)
       return SPDZ_E_NOMEM;
   }
   std::vector<float> X((size_t)B * SPDZ_MLP_IN), Y((size_t)B * SPDZ_MLP_OUT);
@@ -1462,7 +1462,7 @@ extern "C" {
 spdz_status spdz_dag_set_cost_model(spdz_dag *g, const float *W, double ns_per_byte, double ns_per_copy) {
   if (!g || !W || ns_per_byte < 0 || ns_per_copy < 0) return SPDZ_E_INVAL;
   SPDZ_RET(ensure_stream(g));
-  if (!g->d_model && hipMalloc((void **)&g->d_model, SPDZ_MLP_NPARAM * sizeof(float)) != hipSuccess) return SPDZ_E_NOMEM;
+  if (!g->d_model && dev_alloc(&g->d_model, SPDZ_MLP_NPARAM * sizeof(float)) != hipSuccess) return SPDZ_E_NOMEM;
   g->cost_model.assign(W, W + SPDZ_MLP_NPARAM);
   g->learned_on_gpu.clear();
   g->learned_gpu_ns.clear();
@@ -1481,9 +1481,9 @@ spdz_status spdz_dag_time_transfer(spdz_ctx *c, int64_t words, int reps, double 
   std::vector<XferSeg> segs;
   add_segs(segs, 0, 0, words, 0);
   spdz_status s = SPDZ_OK;
-  if (hipMalloc((void **)&dev, (size_t)words * 8) != hipSuccess ||
-      hipMalloc(&dsegs, segs.size() * sizeof(XferSeg)) != hipSuccess ||
-      hipHostMalloc((void **)&host, (size_t)words * 8, hipHostMallocMapped) != hipSuccess)
+  if (dev_alloc(&dev, (size_t)words * 8) != hipSuccess ||
+      dev_alloc(&dsegs, segs.size() * sizeof(XferSeg)) != hipSuccess ||
+      host_alloc(&host, (size_t)words * 8, hipHostMallocMapped) != hipSuccess)
     s = SPDZ_E_NOMEM;
   if (s == SPDZ_OK && hipHostGetDevicePointer((void **)&hdev, host, 0) != hipSuccess) s = SPDZ_E_HIP;
   if (s == SPDZ_OK)
@@ -1542,7 +1542,7 @@ spdz_status spdz_dag_time_level(spdz_ctx *c, int kind, int64_t width, int64_t q,
   spdz_status s = spdz_dag_deal(g, 0x5EED, 1 << 20, 1 << 21);
   if (s == SPDZ_OK) s = ensure_stream(g);
   if (s == SPDZ_OK && !g->tune_acc &&
-      hipMalloc((void **)&g->tune_acc, (size_t)MAX_SLOTS * (MAX_PARTIES + 1) * sizeof(u64)) != hipSuccess)
+      dev_alloc(&g->tune_acc, (size_t)MAX_SLOTS * (MAX_PARTIES + 1) * sizeof(u64)) != hipSuccess)
     s = SPDZ_E_NOMEM;
   if (s == SPDZ_OK) s = set_params(g);
   if (s != SPDZ_OK) return fin(s);

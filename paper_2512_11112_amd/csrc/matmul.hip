@@ -485,13 +485,22 @@ __global__ __launch_bounds__(256) void k_crt(const CrtArgs A) {
 // ==========================================================================
 spdz_status ensure_ws(spdz_ctx *c, size_t bytes) {
   if (c->ws_bytes >= bytes) return SPDZ_OK;
+  // (beyond a context's limit: more than any device has, so that the refusal is the runtime's own)
+  const size_t ask = c->ws_limit && bytes > c->ws_limit ? (size_t)1 << 60 : bytes;
+  void *fresh = nullptr;
+  bool had = dev_alloc(&fresh, ask) == hipSuccess;
   if (c->ws) {
-    if (hipStreamSynchronize(c->stream) != hipSuccess) return SPDZ_E_HIP;
+    if (hipStreamSynchronize(c->stream) != hipSuccess) {
+      if (had) hipFree(fresh);
+      return SPDZ_E_HIP;
+    }
     hipFree(c->ws);
     c->ws = nullptr;
     c->ws_bytes = 0;
+    had = had || dev_alloc(&fresh, ask) == hipSuccess;
   }
-  if (hipMalloc(&c->ws, bytes) != hipSuccess) return SPDZ_E_NOMEM;
+  if (!had) return SPDZ_E_NOMEM;
+  c->ws = fresh;
   c->ws_bytes = bytes;
   return SPDZ_OK;
 }

@@ -329,7 +329,8 @@ spdz_status spdz_mlp_backward(void *stream, const float *W, const float *X, cons
   // one chunk writes the gradient itself; more leave partial sums (of up to 256 blocks) for a second pass
   const int64_t parts = std::min<int64_t>((B + CHUNK - 1) / CHUNK, 256);
   float *part = dW;
-  if (parts > 1 && hipMallocAsync((void **)&part, (size_t)parts * NPARAM * sizeof(float), st) != hipSuccess)
+  if (parts > 1 &&
+      no_error(hipMallocAsync((void **)&part, (size_t)parts * NPARAM * sizeof(float), st)) != hipSuccess)
     return SPDZ_E_NOMEM;
   hipLaunchKernelGGL(k_mlp_backward, dim3((unsigned)parts, 3), dim3(512), 0, st, W, X, acts, dY, B, part);
   if (parts > 1) hipLaunchKernelGGL(k_mlp_sum, dim3(blocks(NPARAM)), dim3(256), 0, st, part, (int)parts, dW);
@@ -356,8 +357,8 @@ spdz_status spdz_mlp_train(void *stream, float *W, const float *X, const float *
   int32_t *d_idx = nullptr;
   const size_t nb = (size_t)Bm * IN + (size_t)Bm * OUT * 3 + (size_t)3 * Bm * HID + 3 * (size_t)NPARAM +
                     (size_t)N * OUT;
-  if (hipMalloc((void **)&buf, nb * sizeof(float)) != hipSuccess) return SPDZ_E_NOMEM;
-  if (hipMalloc((void **)&d_idx, (size_t)N * sizeof(int32_t)) != hipSuccess) {
+  if (dev_alloc(&buf, nb * sizeof(float)) != hipSuccess) return SPDZ_E_NOMEM;
+  if (dev_alloc(&d_idx, (size_t)N * sizeof(int32_t)) != hipSuccess) {
     (void)hipFree(buf);
     return SPDZ_E_NOMEM;
   }

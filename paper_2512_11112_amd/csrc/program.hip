@@ -715,7 +715,7 @@ spdz_status alloc_shares(spdz_prog *g, spdz_shares &s, int64_t w) {
   const spdz_ctx *c = g->c;
   const size_t words = (size_t)c->n * c->L * w;
   u64 *v = nullptr;
-  if (hipMalloc((void **)&v, 2 * words * 8) != hipSuccess) return SPDZ_E_NOMEM;
+  if (dev_alloc(&v, 2 * words * 8) != hipSuccess) return SPDZ_E_NOMEM;
   s = spdz_shares{v, v + words, w, c->L * w, w};
   return SPDZ_OK;
 }
@@ -724,7 +724,7 @@ spdz_status alloc_shares(spdz_prog *g, spdz_shares &s, int64_t w) {
 spdz_status alloc_shares32(spdz_prog *g, spdz_shares32 &s, int64_t w) {
   const size_t words = (size_t)g->c->n * w;
   u32 *v = nullptr;
-  if (hipMalloc((void **)&v, 2 * words * 4) != hipSuccess) return SPDZ_E_NOMEM;
+  if (dev_alloc(&v, 2 * words * 4) != hipSuccess) return SPDZ_E_NOMEM;
   s = spdz_shares32{v, v + words, w, w};
   return SPDZ_OK;
 }
@@ -751,8 +751,8 @@ spdz_status alloc_buffers(spdz_prog *g) {
     PNode &n = kv.second;
     if (n.secret) SPDZ_RET(alloc_shares(g, n.sh, n.width));
     // public values: device and pinned host words
-    if (!n.secret && hipMalloc((void **)&n.dpub, (size_t)c->L * n.width * 8) != hipSuccess) return SPDZ_E_NOMEM;
-    if (!n.secret && hipHostMalloc((void **)&n.hpub, (size_t)c->L * n.width * 8, hipHostMallocDefault) != hipSuccess)
+    if (!n.secret && dev_alloc(&n.dpub, (size_t)c->L * n.width * 8) != hipSuccess) return SPDZ_E_NOMEM;
+    if (!n.secret && host_alloc(&n.hpub, (size_t)c->L * n.width * 8, hipHostMallocDefault) != hipSuccess)
       return SPDZ_E_NOMEM;
     const bool ss = n.op == OP_MUL && g->nodes[n.args[0]].secret && g->nodes[n.args[1]].secret;
     if (ss) {
@@ -765,7 +765,7 @@ spdz_status alloc_buffers(spdz_prog *g) {
       SPDZ_RET(alloc_shares(g, n.tri.a, dout * din));
       SPDZ_RET(alloc_shares(g, n.tri.b, tiles * din));
       SPDZ_RET(alloc_shares(g, n.tri.c, dout));
-      if (hipMalloc((void **)&n.ltmp, (size_t)(dout * din + tiles * din + dout) * 8) != hipSuccess) return SPDZ_E_NOMEM;
+      if (dev_alloc(&n.ltmp, (size_t)(dout * din + tiles * din + dout) * 8) != hipSuccess) return SPDZ_E_NOMEM;
       if (!g->nodes[n.args[2]].secret) SPDZ_RET(alloc_shares(g, n.bsh, dout));
       if (c->fid == FID_32) {  // the packed kernel's operands and the packed triple of a run-time deal
         SPDZ_RET(alloc_shares32(g, n.pkW, dout * din));
@@ -982,7 +982,7 @@ spdz_status upload_words(spdz_prog *g, u64 *dst, const u64 *src, size_t words) {
       if (g->arena) hipHostFree(g->arena);
       g->arena = nullptr;
       g->arena_words = std::max(words, (size_t)1 << 20);
-      if (hipHostMalloc((void **)&g->arena, g->arena_words * 8, hipHostMallocDefault) != hipSuccess) {
+      if (host_alloc(&g->arena, g->arena_words * 8, hipHostMallocDefault) != hipSuccess) {
         g->arena_words = 0;
         return SPDZ_E_NOMEM;
       }

@@ -190,3 +190,44 @@ def test_matmul_panels_match_valu_engine():
         out.append(Z)
     assert torch.equal(out[0].val, out[1].val) and torch.equal(out[0].mac, out[1].mac)
     ctx.close()
+
+
+@pytest.mark.parametrize("n,M,K,N,limit", [
+    (2, 300, 1362, 160, 40 << 20),    # tiles of 128 x 128: whole 79 MB, one tile 30 MB
+    (4, 900, 64, 900, 9 << 20),       # 256 x 128: whole 155 MB, 256 x 256 13 MB, one tile 8 MB
+    (2, 1000, 2200, 1000, 120 << 20), # 256 x 256, 18 moduli: whole 466 MB, one tile 103 MB
+])
+def test_matmul_short_workspace(monkeypatch, n, M, K, N, limit):
+    """A context whose workspace is refused beyond a limit (by the runtime itself: the library asks for what no
+    device has) runs a product in smaller panels, down to one tile; below that the call does nothing but say so."""
+    from paper_2512_11112_amd import spdz as S
+    seed = 6
+
+    def context(bytes_):
+        if bytes_:
+            monkeypatch.setenv("SPDZ_WORKSPACE_LIMIT", str(bytes_))
+        else:
+            monkeypatch.delenv("SPDZ_WORKSPACE_LIMIT", raising=False)
+        return S.Context(n, P61, S.deal_alpha(P61, n, seed), seed)
+    whole = context(0)
+    X = whole.spdz_deal_secret(seed, ARR_MX, S.ShareTensor.empty(n, 1, M * K))
+    Y = whole.spdz_deal_secret(seed, ARR_MX + 1, S.ShareTensor.empty(n, 1, K * N))
+    T = whole.spdz_deal_matrix_triple(seed, ARR_MX + 2, M, K, N, S.TripleTensor.empty_matrix(n, M, K, N))
+
+    def product(ctx, variant):
+        Z = S.ShareTensor.empty(n, 1, M * N)
+        E, Fo = (torch.empty((1, w), dtype=torch.int64, device="cuda") for w in (M * K, K * N))
+        ctx.spdz_matmul_triple(M, K, N, X, Y, T, Z, E, Fo, variant)
+        assert ctx.spdz_mac_check()[0]
+        return Z.val, Z.mac, E, Fo
+    ref = product(whole, 0)
+    bounded, short = context(limit), context(1 << 20)
+    for ctx in (bounded, bounded, whole):  # the second finds the first one's workspace
+        assert all(torch.equal(a, b) for a, b in zip(product(ctx, 1), ref))
+    with pytest.raises(S.SpdzError) as e:
+        product(short, 1)
+    assert e.value.status == -4 and short.opened_count() == 0  # SPDZ_E_NOMEM
+    assert torch.equal(short.spdz_open(X), whole.spdz_open(X))  # the failure is not the next call's
+    assert short.spdz_mac_check()[0] and whole.spdz_mac_check()[0]
+    for ctx in (bounded, short, whole):
+        ctx.close()
