@@ -279,9 +279,10 @@ spdz_status spdz_linear_layer32(spdz_ctx *ctx, int64_t dout, int64_t din, int64_
  *          1 = exact int8 MFMA GEMMs modulo 17 or 18 byte-sized coprime numbers, joined by the
  *              Chinese remainder theorem (K <= 8191, else SPDZ_E_SHAPE),
  *         -1 = library choice (MFMA).
- * Grows a library-owned workspace on first use (for the MFMA variant 18 ((2 n + 1) (M K + K N) +
- * 2 n M N) bytes with the sizes rounded up to whole tiles, at least 64 MB where it can be had, at most
- * 8 GiB while one tile of each side fits: larger products run in panels); the call is asynchronous. */
+ * Grows a library-owned workspace on first use, unless the triple was dealt in this context (for the
+ * MFMA variant 18 ((2 n + 1) (M K + K N) + 2 n M N) bytes with the sizes rounded up to whole tiles, at
+ * most 8 GiB while one tile of each side fits: larger products run in panels, and so do those whose
+ * workspace cannot be had); the call is asynchronous. */
 spdz_status spdz_matmul_triple(spdz_ctx *ctx, int64_t M, int64_t K, int64_t N, const spdz_shares *X,
                                const spdz_shares *Y, const spdz_triple *T, spdz_shares *Z,
                                uint64_t *E_pub, uint64_t *F_pub, int variant);
@@ -582,7 +583,8 @@ spdz_status spdz_deal_secret(spdz_ctx *ctx, uint64_t seed, uint64_t array_id,
 
 /* Deal a matrix triple: A [M][K] from array_id, B [K][N] from array_id + 1,
  * C = A B mod p shared with array_id + 2 (p = 2^61 - 1 only; K <= 8191).
- * Synchronous: allocates and frees a temporary buffer for the public values. */
+ * Synchronous: allocates and frees a temporary buffer for the public values, and grows the
+ * context's workspace to what spdz_matmul_triple takes for these sizes, where it is to be had. */
 spdz_status spdz_deal_matrix_triple(spdz_ctx *ctx, uint64_t seed, uint64_t array_id, int64_t M, int64_t K,
                                     int64_t N, spdz_triple *out);
 

@@ -483,26 +483,35 @@ __global__ __launch_bounds__(256) void k_crt(const CrtArgs A) {
 // ==========================================================================
 // host side
 // ==========================================================================
-spdz_status ensure_ws(spdz_ctx *c, size_t bytes) {
-  if (c->ws_bytes >= bytes) return SPDZ_OK;
+// takes a workspace of `bytes` in the old one's place, both held together; nothing changes where that fails
+static spdz_status swap_ws(spdz_ctx *c, size_t bytes) {
   // (beyond a context's limit: more than any device has, so that the refusal is the runtime's own)
   const size_t ask = c->ws_limit && bytes > c->ws_limit ? (size_t)1 << 60 : bytes;
   void *fresh = nullptr;
-  bool had = dev_alloc(&fresh, ask) == hipSuccess;
+  if (dev_alloc(&fresh, ask) != hipSuccess) return SPDZ_E_NOMEM;
   if (c->ws) {
     if (hipStreamSynchronize(c->stream) != hipSuccess) {
-      if (had) hipFree(fresh);
+      hipFree(fresh);
       return SPDZ_E_HIP;
     }
     hipFree(c->ws);
-    c->ws = nullptr;
-    c->ws_bytes = 0;
-    had = had || dev_alloc(&fresh, ask) == hipSuccess;
   }
-  if (!had) return SPDZ_E_NOMEM;
   c->ws = fresh;
   c->ws_bytes = bytes;
   return SPDZ_OK;
+}
+
+spdz_status ensure_ws(spdz_ctx *c, size_t bytes) {
+  if (c->ws_bytes >= bytes) return SPDZ_OK;
+  spdz_status s = swap_ws(c, bytes);
+  if (s == SPDZ_E_NOMEM && c->ws) {
+    SPDZ_RET(hip_status(hipStreamSynchronize(c->stream)));
+    hipFree(c->ws);
+    c->ws = nullptr;
+    c->ws_bytes = 0;
+    s = swap_ws(c, bytes);
+  }
+  return s;
 }
 
 namespace {
@@ -534,15 +543,22 @@ struct RnsProblem {
 struct RnsPlan {
   int64_t pm, pn;           // panel size
   size_t lbytes, rbytes, sbytes;
+  size_t bytes() const { return lbytes + rbytes + sbytes; }
 };
 
-// largest workspace taken without trying panels, and the least: allocations up to it take 14 us, beyond 92
-// (and 310 to free), and a small product after the dealer's smaller still does not allocate again
-constexpr size_t RNS_WS = (size_t)8 << 30, RNS_WS_MIN = (size_t)64 << 20;
+constexpr size_t RNS_WS = (size_t)8 << 30;  // largest workspace taken without trying panels
 
-RnsPlan rns_plan(const RnsProblem &P, int T, int tm, int tn, int64_t pm, int64_t pn) {
+RnsPlan rns_plan(const RnsProblem &P, int T, int64_t pm, int64_t pn) {
   const int64_t kp = up(P.K, 64);
   return RnsPlan{pm, pn, (size_t)P.nl * T * pm * kp, (size_t)P.nr * T * pn * kp, (size_t)P.nz * T * pm * pn};
+}
+
+// the largest panels within RNS_WS, down to one tile
+RnsPlan rns_first_plan(const RnsProblem &P, int T, int tm, int tn) {
+  int64_t pm = up(P.M, tm), pn = up(P.N, tn);
+  while (rns_plan(P, T, pm, pn).bytes() > RNS_WS && smaller_panel(pm, pn, tm, tn)) {
+  }
+  return rns_plan(P, T, pm, pn);
 }
 
 template <int T, int WM, int WN, int NB>
@@ -623,28 +639,23 @@ spdz_status rns_panels(spdz_ctx *c, const RnsProblem &P, const RnsPlan &plan, ch
 template <int T, int WM, int WN, int NB, class Open>
 spdz_status rns_run(spdz_ctx *c, RnsProblem &P, size_t head, int bpc, Open &&open) {
   constexpr int tm = 64 * WM, tn = 64 * WN;
-  int64_t pm = up(P.M, tm), pn = up(P.N, tn);
+  RnsPlan plan = rns_first_plan(P, T, tm, tn);
   for (;;) {
-    const RnsPlan plan = rns_plan(P, T, tm, tn, pm, pn);
-    const size_t need = head + plan.lbytes + plan.rbytes + plan.sbytes;
-    const bool last = pm <= tm && pn <= tn;
-    if (need <= RNS_WS + head || last) {
-      spdz_status s = c->ws_bytes >= need ? SPDZ_OK : ensure_ws(c, std::max(need, RNS_WS_MIN));
-      if (s == SPDZ_E_NOMEM && need < RNS_WS_MIN) s = ensure_ws(c, need);
-      if (s == SPDZ_OK) {
-        char *ws = (char *)c->ws;
-        SPDZ_RET(open(ws));
-        return rns_panels<T, WM, WN, NB>(c, P, plan, ws + head, bpc);
-      }
-      if (s != SPDZ_E_NOMEM || last) return s;
+    const spdz_status s = ensure_ws(c, head + plan.bytes());
+    if (s == SPDZ_OK) {
+      char *ws = (char *)c->ws;
+      SPDZ_RET(open(ws));
+      return rns_panels<T, WM, WN, NB>(c, P, plan, ws + head, bpc);
     }
-    smaller_panel(pm, pn, tm, tn);
+    if (s != SPDZ_E_NOMEM || !smaller_panel(plan.pm, plan.pn, tm, tn)) return s;
+    plan = rns_plan(P, T, plan.pm, plan.pn);
   }
 }
 
-template <class Open>
-spdz_status rns_product(spdz_ctx *c, RnsProblem &P, size_t head, Open &&open) {
-  auto go = [&](auto tt) -> spdz_status {
+// fn(moduli, WM, WN, stage buffers, blocks per CU) for the problem's moduli and tiling
+template <class Fn>
+auto rns_tiling(const spdz_ctx *c, const RnsProblem &P, Fn &&fn) {
+  auto go = [&](auto tt) {
     constexpr int T = decltype(tt)::value;
     // Relative time of a tiling: whole rounds of the resident blocks, each as long as its tile's products
     // and the reduction of its sums (in inner indices: 340 where one block a CU leaves the matrix cores
@@ -657,13 +668,39 @@ spdz_status rns_product(spdz_ctx *c, RnsProblem &P, size_t head, Open &&open) {
       return (double)(rounds * slots) * wm * wn * ((double)P.K * P.npairs + idle) / rate;
     };
     const double c44 = cost(4, 4, 1, 340, 1.0), c42 = cost(4, 2, 2, 170, 0.93), c22 = cost(2, 2, 2, 170, 0.8);
-    if (c44 <= c42 && c44 <= c22) return rns_run<T, 4, 4, 4>(c, P, head, 1, open);
-    if (c42 <= c22) return rns_run<T, 4, 2, 3>(c, P, head, 2, open);
-    return rns_run<T, 2, 2, 4>(c, P, head, 2, open);
+    using std::integral_constant;
+    if (c44 <= c42 && c44 <= c22)
+      return fn(tt, integral_constant<int, 4>{}, integral_constant<int, 4>{}, integral_constant<int, 4>{}, 1);
+    if (c42 <= c22)
+      return fn(tt, integral_constant<int, 4>{}, integral_constant<int, 2>{}, integral_constant<int, 3>{}, 2);
+    return fn(tt, integral_constant<int, 2>{}, integral_constant<int, 2>{}, integral_constant<int, 4>{}, 2);
   };
   if (P.K * P.npairs <= rns::T17_TERMS) return go(std::integral_constant<int, 17>{});
   return go(std::integral_constant<int, 18>{});
 }
+
+template <class Open>
+spdz_status rns_product(spdz_ctx *c, RnsProblem &P, size_t head, Open &&open) {
+  return rns_tiling(c, P, [&](auto t, auto wm, auto wn, auto nb, int bpc) {
+    return rns_run<decltype(t)::value, decltype(wm)::value, decltype(wn)::value, decltype(nb)::value>(c, P, head, bpc,
+                                                                                                      open);
+  });
+}
+
+// the sizes of a matrix triple's product
+RnsProblem triple_problem(int n, int64_t M, int64_t K, int64_t N) {
+  RnsProblem P;
+  memset(&P, 0, sizeof(P));
+  P.M = M;
+  P.K = K;
+  P.N = N;
+  P.nl = P.nr = 1 + 2 * n;
+  P.nz = 2 * n;
+  P.npairs = 2;
+  return P;
+}
+
+size_t up256(size_t b) { return (b + 255) / 256 * 256; }
 
 }  // namespace
 
@@ -672,9 +709,8 @@ spdz_status launch_matmul_triple(spdz_ctx *c, int64_t M, int64_t K, int64_t N, c
                                  int variant) {
   const int n = c->n;
   // workspace: the opened matrices if not supplied and, for the VALU engine, P; then the matrix engine's
-  auto al = [](size_t b) { return (b + 255) / 256 * 256; };
-  const size_t e_bytes = E_pub ? 0 : al((size_t)M * K * 8), f_bytes = F_pub ? 0 : al((size_t)K * N * 8);
-  const size_t p_bytes = variant == 1 ? 0 : al((size_t)M * N * 8), head = e_bytes + f_bytes + p_bytes;
+  const size_t e_bytes = E_pub ? 0 : up256((size_t)M * K * 8), f_bytes = F_pub ? 0 : up256((size_t)K * N * 8);
+  const size_t p_bytes = variant == 1 ? 0 : up256((size_t)M * N * 8), head = e_bytes + f_bytes + p_bytes;
   u64 *E = E_pub, *Fm = F_pub;
   // opens E = X - A (row-major, M K values), then F = Y - B (K N values)
   auto open = [&](char *ws) -> spdz_status {
@@ -687,14 +723,7 @@ spdz_status launch_matmul_triple(spdz_ctx *c, int64_t M, int64_t K, int64_t N, c
   auto c_of = [&](int i, bool mac) { return (mac ? T->c.mac : T->c.val) + i * T->c.party_stride; };
   auto z_of = [&](int i, bool mac) { return (mac ? Z->mac : Z->val) + i * Z->party_stride; };
   if (variant == 1) {
-    RnsProblem P;
-    memset(&P, 0, sizeof(P));
-    P.M = M;
-    P.K = K;
-    P.N = N;
-    P.nl = P.nr = 1 + 2 * n;
-    P.nz = 2 * n;
-    P.npairs = 2;
+    RnsProblem P = triple_problem(n, M, K, N);
     for (int z = 0; z < 2 * n; z++) {
       P.lsrc[z][0] = P.rsrc[z][1] = 0;  // E, F
       P.lsrc[z][1] = P.rsrc[z][0] = 1 + z;
@@ -735,8 +764,16 @@ spdz_status launch_matmul_triple(spdz_ctx *c, int64_t M, int64_t K, int64_t N, c
   return valu_gemm(c, G, 2 * n);
 }
 
-// C = A B mod p for public matrices (used by the dealer of matrix triples)
+// C = A B mod p for public matrices (used by the dealer of matrix triples).  Takes room for the product that
+// will use the triple, where it is to be had: grown from the dealer's own in the first product, the workspace
+// cost that product a wait for the stream and about 300 us of hipFree and hipMalloc (3 parties, 64 x 4000 x 64:
+// 685 us where the second took 116).
 spdz_status launch_public_matmul(spdz_ctx *c, int64_t M, int64_t K, int64_t N, const u64 *Am, const u64 *Bm, u64 *Cm) {
+  const RnsProblem use = triple_problem(c->n, M, K, N);
+  const size_t room = rns_tiling(c, use, [&](auto t, auto wm, auto wn, auto, int) {
+    return rns_first_plan(use, t, 64 * wm, 64 * wn).bytes();
+  }) + up256((size_t)M * K * 8) + up256((size_t)K * N * 8);
+  if (c->ws_bytes < room && swap_ws(c, room) == SPDZ_E_HIP) return SPDZ_E_HIP;
   RnsProblem P;
   memset(&P, 0, sizeof(P));
   P.M = M;

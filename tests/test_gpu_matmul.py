@@ -231,3 +231,23 @@ def test_matmul_short_workspace(monkeypatch, n, M, K, N, limit):
     assert short.spdz_mac_check()[0] and whole.spdz_mac_check()[0]
     for ctx in (bounded, short, whole):
         ctx.close()
+
+
+def test_dealing_makes_room_for_the_product():
+    """A product whose triple was dealt in its context allocates nothing, with the opened matrices kept or not."""
+    from paper_2512_11112_amd import spdz as S
+    n, M, K, N, seed = 3, 64, 4000, 64, 6
+    ctx = S.Context(n, P61, S.deal_alpha(P61, n, seed), seed)
+    X = ctx.spdz_deal_secret(seed, ARR_MX, S.ShareTensor.empty(n, 1, M * K))
+    Y = ctx.spdz_deal_secret(seed, ARR_MX + 1, S.ShareTensor.empty(n, 1, K * N))
+    Z = S.ShareTensor.empty(n, 1, M * N)
+    E, Fo = (torch.empty((1, w), dtype=torch.int64, device="cuda") for w in (M * K, K * N))
+    T = S.TripleTensor.empty_matrix(n, M, K, N)
+    before = torch.cuda.mem_get_info()[0]
+    ctx.spdz_deal_matrix_triple(seed, ARR_MX + 2, M, K, N, T)
+    dealt = torch.cuda.mem_get_info()[0]
+    assert before - dealt >= 18 * (2 * n + 1) * (M + N) * K  # the planes' bytes, without their padding
+    for out in ((E, Fo), (None, None)):
+        ctx.spdz_matmul_triple(M, K, N, X, Y, T, Z, *out)
+        assert ctx.spdz_mac_check()[0] and torch.cuda.mem_get_info()[0] == dealt
+    ctx.close()
