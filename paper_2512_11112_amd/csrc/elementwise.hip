@@ -558,24 +558,39 @@ spdz_status launch_open(spdz_ctx *c, const spdz_shares *x, u64 *out_pub) {
   });
 }
 
-// opens x0 - s0 into out0, then x1 - s1 into out1
+// whether the L len words of a public vector lie inside what x spans
+static bool pub_overlaps(const spdz_ctx *c, const u64 *pub, int64_t len, const spdz_shares *x) {
+  const int64_t span = (int64_t)(c->n - 1) * x->party_stride + (int64_t)(c->L - 1) * x->limb_stride + x->len;
+  for (const u64 *v : {(const u64 *)x->val, (const u64 *)x->mac})
+    if (pub < v + span && v < pub + c->L * len) return true;
+  return false;
+}
+
+// Opens x0 - s0 into out0, then x1 - s1 into out1: in one launch, or one after the other where out1 takes the
+// place of what the first still reads.
 spdz_status launch_open_diffs(spdz_ctx *c, const spdz_shares *x0, const spdz_shares *s0, u64 *out0,
                               const spdz_shares *x1, const spdz_shares *s1, u64 *out1) {
+  const bool apart = pub_overlaps(c, out1, x1->len, x0) || pub_overlaps(c, out1, x1->len, s0);
   return visit(c, [&](auto f, auto nn) -> spdz_status {
     using F = decltype(f);
     constexpr int N = decltype(nn)::value;
-    const OpenDiffsArgs<F, N> a{{sv_of(x0), sv_of(x1)}, {sv_of(s0), sv_of(s1)}, {out0, out1},  {x0->len, x1->len},
-                                coef_state(c),          c->log_count,           c->d_acc};
-    const int64_t W = x0->len + x1->len;
-    const int g = grid_for(c, (const void *)k_open_diffs<F, N>, W);
-    KTimer tm(c, "open");
-    hipLaunchKernelGGL((k_open_diffs<F, N>), dim3(g), dim3(BLOCK), 0, c->stream, a);
-    spdz_status s = hip_status(hipGetLastError());
-    if (s == SPDZ_OK) {
-      c->log_count += W;
-      if (g > c->slots) c->slots = g;
-    }
-    return s;
+    auto run = [&](int64_t w0, int64_t w1) -> spdz_status {
+      const OpenDiffsArgs<F, N> a{{sv_of(x0), sv_of(x1)}, {sv_of(s0), sv_of(s1)}, {out0, out1}, {w0, w1},
+                                  coef_state(c),          c->log_count,           c->d_acc};
+      const int64_t W = w0 + w1;
+      const int g = grid_for(c, (const void *)k_open_diffs<F, N>, W);
+      KTimer tm(c, "open");
+      hipLaunchKernelGGL((k_open_diffs<F, N>), dim3(g), dim3(BLOCK), 0, c->stream, a);
+      spdz_status s = hip_status(hipGetLastError());
+      if (s == SPDZ_OK) {
+        c->log_count += W;
+        if (g > c->slots) c->slots = g;
+      }
+      return s;
+    };
+    if (!apart) return run(x0->len, x1->len);
+    SPDZ_RET(run(x0->len, 0));
+    return run(0, x1->len);
   });
 }
 

@@ -251,3 +251,29 @@ def test_dealing_makes_room_for_the_product():
         ctx.spdz_matmul_triple(M, K, N, X, Y, T, Z, *out)
         assert ctx.spdz_mac_check()[0] and torch.cuda.mem_get_info()[0] == dealt
     ctx.close()
+
+
+@pytest.mark.parametrize("variant", [0, 1])
+@pytest.mark.parametrize("over", ["val", "mac"])
+def test_matmul_opened_right_matrix_over_the_left_operand(variant, over):
+    """F_pub may take the place of X, which nothing reads once E is open (each operand at the far end of its own
+    buffer, so that a launch of both opens would write F long before it reads X there)."""
+    from paper_2512_11112_amd import spdz as S
+    n, M, K, N, seed = 2, 1200, 600, 1100, 9
+    got = []
+    for place in (False, True):
+        ctx = S.Context(n, P61, S.deal_alpha(P61, n, seed), seed)
+        X = ctx.spdz_deal_secret(seed, ARR_MX, S.ShareTensor.empty(n, 1, M * K))
+        Y = ctx.spdz_deal_secret(seed, ARR_MX + 1, S.ShareTensor.empty(n, 1, K * N))
+        T = ctx.spdz_deal_matrix_triple(seed, ARR_MX + 2, M, K, N, S.TripleTensor.empty_matrix(n, M, K, N))
+        Z, E = S.ShareTensor.empty(n, 1, M * N), torch.empty((1, M * K), dtype=torch.int64, device="cuda")
+        Fo = torch.empty((1, K * N), dtype=torch.int64, device="cuda")
+        if place:
+            Fo = getattr(X, over).view(-1)[-K * N:].view(1, K * N)
+        ctx.spdz_matmul_triple(M, K, N, X, Y, T, Z, E, Fo, variant)
+        ok, sigma = ctx.spdz_mac_check()
+        got.append((Z.val, Z.mac, E, Fo.clone()))
+        assert ok and (not place or sigma == first)
+        first = sigma
+        ctx.close()
+    assert all(torch.equal(a, b) for a, b in zip(*got))
