@@ -962,6 +962,7 @@ spdz_status flush(spdz_prog *g) {
   if (J.nins == 0) return SPDZ_OK;
   const int nins = J.nins;
   J.nins = 0;
+  g->launches++;
   return launch_fused(g->c, J.ins, nins, J.nslots, J.width);
 }
 
@@ -1175,7 +1176,6 @@ spdz_status issue_group(spdz_prog *g, FGroup &G) {
     SPDZ_RET(flush(g));
     if (!join(g, G, ins, JOIN_KEPT) && !join(g, G, ins, 0)) return fail(g, "a fused group does not fit a launch");
   }
-  g->launches++;  // (a run counts one, however many share a launch)
   for (int id : G.members) {
     PNode &n = N[id];
     n.pending = false;
@@ -1435,7 +1435,7 @@ spdz_status issue(spdz_prog *g, PNode &n) {
       PNode &a = N[n.args[0]];
       if (n.secret) {
         st = launch_reduce(c, &a.sh, &n.sh);
-        g->launches += 2;
+        g->launches++;
       } else {
         host_visit([&](auto f) { host_reduce<decltype(f)>(a.hpub, a.width, n.hpub); });
         if (n.dev_use) st = upload(g, n);

@@ -484,3 +484,21 @@ def test_output_into_strided_shares(p, n, layout):
         assert not left.any()
     prog.close()
     ctx.close()
+
+
+@pytest.mark.parametrize("p,n,W,trips", [(P_PAPER, 2, 64, 20), (P61, 2, 70000, 9), (P127, 2, 77, 1)])
+@pytest.mark.parametrize("fuse", [True, False])
+def test_launch_counter_counts_launches(p, n, W, trips, fuse):
+    """spdz_prog_stats counts a launch of several fused runs, and a sum, as the one launch it is: the kernel timer
+    of the same run, which brackets each launch, saw as many (triples dealt ahead, phis handed over)."""
+    from paper_2512_11112_amd import spdz as S
+    ctx = S.Context(n, p, S.deal_alpha(p, n, 5), 5)
+    prog = S.Program(ctx, P.loop_program(W, trips), fuse=fuse)
+    prog.predeal(5, trips)
+    ctx.spdz_timing_enable(True)
+    assert prog.run(5)[0]
+    timed = {k: ctx.spdz_timing_get(k)[1] for k in ("fused", "beaver", "linear", "reduce", "open")}
+    assert timed["reduce"] == timed["open"] == 1 and (timed["fused"] > 0) == fuse
+    assert prog.stats()["launches"] == sum(timed.values())
+    prog.close()
+    ctx.close()
