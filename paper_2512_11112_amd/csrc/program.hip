@@ -1752,17 +1752,22 @@ spdz_status spdz_prog_output(spdz_prog *g, int node, spdz_shares *out_shares, ui
   if (n.secret) {
     if (!out_shares || out_shares->len != n.width) return SPDZ_E_SHAPE;
     // the planes of values and of MAC shares: all in one copy each where they are equally spaced (a copy is
-    // about 9 us of the stream), else the parties' planes of a limb, else one by one
+    // about 9 us of the stream), else the parties' planes of a limb, else, and where they lie further apart than
+    // the rows of a copy may, one by one
     const int64_t ps = out_shares->party_stride, ls = out_shares->limb_stride, w = n.width;
-    const bool all = c->L == 1 || ps == c->L * ls, rows = all || ps >= w;
-    const int64_t pitch = all && c->L > 1 ? ls : ps;
+    const bool all = c->L == 1 || ps == c->L * ls;
+    const int64_t pitch = all && c->L > 1 ? ls : ps, src_pitch = (all ? 1 : c->L) * w;
     const int per = all ? c->n * c->L : c->n, copies = all ? 1 : c->L;  // rows of a copy, copies
+    int dev = 0, most = 0;
+    SPDZ_RET(hip_status(no_error(hipGetDevice(&dev))));
+    SPDZ_RET(hip_status(no_error(hipDeviceGetAttribute(&most, hipDeviceAttributeMaxPitch, dev))));
+    const bool rows = pitch >= w && std::max(pitch, src_pitch) <= most / 8;
     for (int h = 0; h < 2; h++) {
       u64 *dst = h ? out_shares->mac : out_shares->val;
       const u64 *src = h ? n.sh.mac : n.sh.val;
-      if (rows && pitch >= w) {
+      if (rows) {
         for (int l = 0; l < copies; l++)
-          if (hipMemcpy2DAsync(dst + l * ls, pitch * 8, src + l * w, (all ? 1 : c->L) * w * 8, w * 8, per,
+          if (hipMemcpy2DAsync(dst + l * ls, pitch * 8, src + l * w, src_pitch * 8, w * 8, per,
                                hipMemcpyDeviceToDevice, c->stream) != hipSuccess)
             return SPDZ_E_HIP;
         continue;

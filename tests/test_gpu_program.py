@@ -502,3 +502,25 @@ def test_launch_counter_counts_launches(p, n, W, trips, fuse):
     assert prog.stats()["launches"] == sum(timed.values())
     prog.close()
     ctx.close()
+
+
+@pytest.mark.parametrize("apart", [(1 << 28) - 1, 1 << 28])
+def test_output_into_shares_far_apart(apart):
+    """spdz_prog_output where the parties' planes lie as far apart as the rows of one copy may (2^31 - 1 bytes on
+    this device), and further."""
+    import ctypes
+    from paper_2512_11112_amd import spdz as S
+    W, n = 300, 2
+    ctx = ctx_for(P_PAPER, n, 4, 5)
+    prog = S.Program(ctx, P.loop_program(W, 2), fuse=True)
+    assert prog.run(4)[0]
+    ref = prog.output(6)
+    val, mac = (torch.zeros((n - 1) * apart + W, dtype=torch.int64, device="cuda") for _ in range(2))
+    d = S.Shares(val=val.data_ptr(), mac=mac.data_ptr(), len=W, party_stride=apart, limb_stride=W)
+    assert S.lib().spdz_prog_output(prog._h, 6, ctypes.byref(d), None) == 0
+    for got, want in ((val, ref.val), (mac, ref.mac)):
+        for i in range(n):
+            assert torch.equal(got[i * apart:i * apart + W], want[i, 0])
+        assert int((got != 0).sum()) == int((want != 0).sum())
+    prog.close()
+    ctx.close()
