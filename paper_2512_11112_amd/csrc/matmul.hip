@@ -28,6 +28,8 @@
 
 namespace spdz {
 
+static_assert(2 * MAX_MFMA_K <= rns::MAX_TERMS, "the concatenated inner dimension of two operand pairs");
+
 constexpr int MAXOUT = 2 * MAX_PARTIES;
 constexpr int TILE = 64;
 
@@ -378,7 +380,7 @@ __global__ __launch_bounds__(256, WM * WN >= 16 ? 1 : 2) void k_rns_gemm(const R
 #pragma unroll
         for (int j = 0; j < WN; j++) asm volatile("" : "+a"(acc[i][j]));
     }
-    // the sums mod m_t, a byte each (|sum| <= 16382 * 127^2 < 2^28)
+    // the sums mod m_t, a byte each (|sum| <= 16382 * 128^2 < 2^28)
     const int per = A.tx * A.ty, gz = idx / per, t = gz / A.nz, z = gz - t * A.nz;
     const float inv = rns::TAB18.inv[t];
     const int neg = rns::TAB18.neg[t], c14 = rns::TAB18.c14[t];

@@ -26,6 +26,14 @@ constexpr int MODS[TMAX] = {256, 253, 251, 249, 247, 241, 239, 235, 233, 229, 22
 // tolerates an error of 0.05, its own is below 3e-4); all 18 give 2^140.79
 constexpr int64_t T17_TERMS = 4287;
 constexpr int64_t MAX_TERMS = 16382;
+static_assert(MAX_TERMS * 128 * 128 < (int64_t)1 << 28, "sums of bytes for round_mod28 (within 0.02 % of it)");
+// whether sums of `terms` products, each at most 2^120, stay below 0.45 M of the first T moduli
+constexpr bool covered(int T, int64_t terms) {
+  double m = 1;
+  for (int t = 0; t < T; t++) m *= MODS[t];
+  return (double)terms * 0x1p120 < 0.45 * m;
+}
+static_assert(covered(17, T17_TERMS) && !covered(17, T17_TERMS + 1) && covered(18, MAX_TERMS), "moduli");
 constexpr int FRAC = 23;  // u_t / m_t is summed in units of 2^-23
 
 constexpr u64 P = (1ull << 61) - 1;
@@ -114,6 +122,17 @@ constexpr Tables make_tables(int T) {
 }
 
 constexpr Tables TAB17 = make_tables(17), TAB18 = make_tables(18);
+
+// round_mod28's argument, |s >> 14| <= 2^14 times c14 and 14 more bits over the bias, stays the bits of a float
+// 2^23 + v with 0 < v < 2^23
+constexpr bool bias14_holds() {
+  for (int t = 0; t < TMAX; t++) {
+    const int64_t b = (int64_t)TAB18.bias14[t] - 0x4B000000, c = TAB18.c14[t] < 0 ? -TAB18.c14[t] : TAB18.c14[t];
+    if (b % 16384 != 0 || b <= c * 16384 || b + c * 16384 + 16383 >= 1 << 23) return false;
+  }
+  return true;
+}
+static_assert(bias14_holds(), "round_mod28");
 template <int T>
 constexpr const Tables &tab() {
   if constexpr (T == 17) return TAB17;
@@ -129,7 +148,8 @@ __device__ __forceinline__ u64 digits(u64 w) {
 // Low byte of r = s - m round(s / m) for the integer s in fb = bias + s, the bits of the float
 // n m + s: its product with 1 / m plus 1.5 2^23 leaves n + round(s / m) in the low mantissa bits, the
 // 24-bit product takes them as they are, and the 2^22 m that the constant contributes is 0 mod 256.
-// The rounded inverse moves the quotient by less than 0.006, so |r| <= 127.
+// The rounded inverse moves the quotient by less than 0.006: |r| <= 127 for the odd moduli; modulo 256 the
+// inverse is exact and a tie may be 128 or -128, which are one byte, -128.
 __device__ __forceinline__ int round_mod(u32 fb, float inv, int neg) {
   float x;
   __builtin_memcpy(&x, &fb, 4);

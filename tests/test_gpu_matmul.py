@@ -5,6 +5,8 @@ the 4096-wide workload on 4096 sampled entries computed one by one by the
 oracle, on Freivalds' check of the reconstructed product and of its MAC, and on
 the MAC-check sigma (which only depends on the opened E and F).
 """
+import math
+
 import numpy as np
 import pytest
 import torch
@@ -277,3 +279,37 @@ def test_matmul_opened_right_matrix_over_the_left_operand(variant, over):
         first = sigma
         ctx.close()
     assert all(torch.equal(a, b) for a, b in zip(*got))
+
+
+LARGEST, SMALLEST = (1 << 60) - 1, 1 << 60  # balanced: 2^60 - 1 and -(2^60 - 1)
+
+
+@pytest.mark.parametrize("K,left,right", [
+    (2143, LARGEST, LARGEST), (2143, LARGEST, SMALLEST),  # 0.4499 M of 17 moduli, both signs
+    (2144, LARGEST, LARGEST), (8191, LARGEST, LARGEST), (8191, LARGEST, SMALLEST),  # 18 moduli
+    (8191, 128, 128), (8191, 128, 127),  # bytes mod 256: all -128 (sums 0.02 % below 2^28), -128 by 127
+])
+def test_matmul_sums_at_the_bounds(K, left, right):
+    """Party 1's MAC output is a sum of 2 K equal products of the largest magnitude: its product is
+    [E | M(A)_1] [M(B)_1 + alpha_1 F; F] with E = M(A)_1 = left, M(B)_1 = F = right and alpha_1 = 0."""
+    from oracle.pipelines import DealtMat
+    n, M, N = 2, 3, 5
+    f = F.Field(P61)
+
+    def sh(rows, cols, v0, m1):  # party 0's value shares, party 1's MAC shares
+        val, mac = (np.zeros((n, 1, rows * cols), dtype=np.uint64) for _ in range(2))
+        val[0], mac[1] = v0, m1
+        return F.Shares(val, mac)
+    if max(left, right) >= LARGEST:
+        moduli = [256, 253, 251, 249, 247, 241, 239, 235, 233, 229, 227, 223, 217, 211, 199, 197, 193]
+        assert (2 * K * LARGEST ** 2 / math.prod(moduli) > 0.4498) and (K > 2143 or 2 * K * LARGEST ** 2 < 0.45 * math.prod(moduli))
+    X, Y, A, B = sh(M, K, left, 0), sh(K, N, right, 0), sh(M, K, 0, left), sh(K, N, 0, right)
+    C = sh(M, N, 0, 0)
+    al = np.array([[1], [0]], dtype=np.uint64)
+    D = DealtMat(f, n, 0, M, K, N, al, None, X, None, Y, F.TripleArr(A, B, C))
+    ref = matrix_triple_run(D, check_seed=6)
+    balanced = [w if w < SMALLEST else w - P61 for w in (left, right)]
+    assert (ref["Z"].mac[1] == 2 * K * balanced[0] * balanced[1] % P61).all()
+    Z, E, Fo, ok, sigma = run_device(D, 1, 6)
+    assert np.array_equal(host(Z.val), ref["Z"].val) and np.array_equal(host(Z.mac), ref["Z"].mac)
+    assert ok == ref["ok"] and sigma == ints_of_sigma(ref["sigma"])
