@@ -524,3 +524,52 @@ def test_output_into_shares_far_apart(apart):
         assert int((got != 0).sum()) == int((want != 0).sum())
     prog.close()
     ctx.close()
+
+
+@pytest.mark.parametrize("past", [0, 1])
+@pytest.mark.parametrize("p,n,lanes", [(P_PAPER, 2, 4), (P61, 2, 4), (P127, 2, 4), (P61, 3, 8), (P_PAPER, 4, 8),
+                                       (P61, 5, 16), (P_PAPER, 8, 16)])
+def test_fused_runs_where_the_kernels_change(p, n, lanes, past):
+    """The largest width of the narrow kernel (two blocks of 256 lanes per CU) and the smallest of the wide one, for
+    each number of lanes per element: outputs and sigma as with every node its own kernel."""
+    from paper_2512_11112_amd import spdz as S
+    W = 2 * torch.cuda.get_device_properties(0).multi_processor_count * 256 // lanes + past
+    for text, outs in ((P.loop_program(W, 4), (6, 15)), (joining_program(W, 4), (6, 18, 14))):
+        got = []
+        for fuse in (True, False):
+            ctx = S.Context(n, p, S.deal_alpha(p, n, 5), 5)
+            prog = S.Program(ctx, text, fuse=fuse)
+            assert prog.n_groups > 0
+            prog.predeal(5, 4)
+            ok, sigma, _ = prog.run(5)
+            assert ok
+            vals = [prog.output(o) for o in outs]
+            got.append((sigma, [t for v in vals for t in ((v.val, v.mac) if hasattr(v, "val") else (v,))]))
+            prog.close()
+            ctx.close()
+        assert got[0][0] == got[1][0]
+        assert all(torch.equal(a, b) for a, b in zip(got[0][1], got[1][1]))
+
+
+@pytest.mark.parametrize("p,n,W", [(P61, 5, 1), (P61, 5, 130), (P_PAPER, 8, 17), (P_PAPER, 8, 130)])
+def test_joined_runs_of_sixteen_lanes(p, n, W):
+    """Runs that share a launch with 16 lanes per element, at partial blocks: the oracle's outputs and sigma."""
+    from paper_2512_11112_amd import spdz as S
+    trips = 9
+    text = joining_program(W, trips)
+    ref = run_program(text, p, n, 5, 5)
+    for ahead in (True, False):
+        ctx = S.Context(n, p, S.deal_alpha(p, n, 5), 5)
+        prog = S.Program(ctx, text)
+        assert prog.n_groups > 0
+        if ahead:
+            prog.predeal(5, trips)
+        ok, sigma, _ = prog.run(5)
+        assert ok and sigma == ints_of_sigma(ref["sigma"])
+        if ahead:
+            assert prog.stats()["launches"] < trips  # (dealt on the fly, each iteration is its own launch)
+        for o in (6, 18, 14):
+            out = prog.output(o)
+            assert np.array_equal(host(out.val), ref["outputs"][o].val) and np.array_equal(host(out.mac), ref["outputs"][o].mac)
+        prog.close()
+        ctx.close()
