@@ -194,11 +194,12 @@ constexpr int FUSED_LDS_BYTES = 61440;  // dynamic LDS of one launch, a thread a
 // bytes of one LDS word of a slot: residues below 2^32 take 4, others 8 per limb
 inline int fused_word_bytes(int fid) { return fid == FID_32 ? 4 : 8; }
 constexpr int FUSED_MAX_SLOTS = 32;  // (over any field and number of parties)
+constexpr int FUSED_MIN_SLOTS = 3;   // a product's operands and its result
 inline int fused_max_slots(int n, int L, int fid) {
   const int most = FUSED_LDS_BYTES / (2 * n * L * fused_word_bytes(fid) * BLOCK);
   return most < FUSED_MAX_SLOTS ? most : FUSED_MAX_SLOTS;
 }
-// slots a list over W elements may use (below 3: none, a product's operands and result do not fit)
+// slots a list over W elements may use (below FUSED_MIN_SLOTS: nothing is fused)
 int fused_slots(const spdz_ctx *c, int64_t W);
 // whether a list of `nslots` slots that loads `operands` buffers can run over W elements, and, for groups
 // joined into one list, whether it keeps to the kernel of the width

@@ -350,13 +350,67 @@ static bool narrow_fits(const spdz_ctx *c, int nslots, int operands, int64_t blo
 // whole where three split it (2^127 - 1, 2 parties, width 64, the loop of launch_fused: 25.7 -> 9.2 us).
 int fused_slots(const spdz_ctx *c, int64_t W) {
   const int wide = fused_max_slots(c->n, c->L, c->fid);
-  return wide >= 3 && narrow_blocks(c, W) > 0 ? std::max(wide, 12) : wide;
+  return wide >= FUSED_MIN_SLOTS && narrow_blocks(c, W) > 0 ? std::max(wide, 12) : wide;
 }
 
 bool fused_runs(const spdz_ctx *c, int nslots, int operands, int64_t W, bool joined) {
   const int64_t blocks = narrow_blocks(c, W);
   if (blocks > 0 && narrow_fits(c, nslots, operands, blocks)) return true;
   return nslots <= fused_max_slots(c->n, c->L, c->fid) && !(joined && blocks > 0);
+}
+
+template <class F, int N>
+static spdz_status launch_list(spdz_ctx *c, const FusedIns *ins, int nins, int nslots, int64_t W) {
+  // narrow: at most two blocks per CU (of BLOCK / LANES elements), and everything the list reads in LDS.
+  // A loop of three products and two additions, joined, us per iteration, narrow / wide: 2^32 - 5, 2 parties,
+  // width 64 2.8 / 7.4, 32768 (two blocks) 4.9 / 7.6, 50000 8.6 / 7.7, 65536 (four) 9.6 / 8.2; 2^61 - 1,
+  // 2 parties, 32768 6.9 / 9.0, 65536 13.7 / 9.9, 3 parties, 16384 (two) 7.5 / 12.6, 32768 13.8 / 12.9.
+  int operands = 0;
+  for (int q = 0; q < nins; q++) operands += fused_operands(ins[q].kind, ins[q].flags);
+  const int64_t blocks = narrow_blocks(c, W);
+  if (blocks > 0 && narrow_fits(c, nslots, operands, blocks)) {
+    NarrowArgs<F, N> A;
+    A.nins = nins;
+    A.nbase = 0;
+    A.nslots = nslots;
+    for (int q = 0; q < nins; q++) {
+      FusedIns I = ins[q];
+      const u64 *p[3] = {I.p0, I.p1, I.p2};
+      const bool pub = I.kind == FK_PUBADD || I.kind == FK_PUBMUL;
+      const u64 mark = !pub ? 0 : (I.flags & FF_PUB_VEC) ? NB_PUB | NB_VEC : NB_PUB;
+      I.reads = (uint8_t)fused_operands(I.kind, I.flags);
+      for (int o = 0; o < I.reads; o++) A.base[A.nbase++] = (u64)(uintptr_t)p[o] | mark;
+      std::memcpy(&A.ins[q].fields, &I, 8);
+      A.ins[q].out = I.out;
+      A.ins[q].j = I.j;
+    }
+    A.W = W;
+    alpha_of<F, N>(c, A.alpha);
+    A.coef_state = coef_state(c);
+    A.acc = c->d_acc;
+    KTimer tm(c, "fused");
+    hipLaunchKernelGGL((k_fused_narrow<F, N>), dim3((unsigned)blocks), dim3(BLOCK),
+                       (size_t)narrow_bytes(c, nslots, operands), c->stream, A);
+    spdz_status s = hip_status(hipGetLastError());
+    if (s == SPDZ_OK && blocks > c->slots) c->slots = (int)blocks;
+    return s;
+  }
+  if (nslots > fused_max_slots(c->n, c->L, c->fid)) return SPDZ_E_INVAL;
+  FusedArgs<F, N> A;
+  for (int q = 0; q < nins; q++) A.ins[q] = ins[q];
+  A.nins = nins;
+  A.W = W;
+  alpha_of<F, N>(c, A.alpha);
+  A.coef_state = coef_state(c);
+  A.acc = c->d_acc;
+  const size_t lds = (size_t)nslots * 2 * N * F::L * fused_word_bytes(c->fid) * BLOCK;
+  const void *k = (const void *)k_fused<F, N>;
+  const int g = grid_for(c, k, W);
+  KTimer tm(c, "fused");
+  hipLaunchKernelGGL((k_fused<F, N>), dim3(g), dim3(BLOCK), lds, c->stream, A);
+  spdz_status s = hip_status(hipGetLastError());
+  if (s == SPDZ_OK && g > c->slots) c->slots = g;
+  return s;
 }
 
 spdz_status launch_fused(spdz_ctx *c, const FusedIns *ins, int nins, int nslots, int64_t W) {
@@ -367,56 +421,10 @@ spdz_status launch_fused(spdz_ctx *c, const FusedIns *ins, int nins, int nslots,
   return visit(c, [&](auto f, auto nn) -> spdz_status {
     using F = decltype(f);
     constexpr int N = decltype(nn)::value;
-    // narrow: at most two blocks per CU (of BLOCK / LANES elements), and everything the list reads in LDS.
-    // A loop of three products and two additions, joined, us per iteration, narrow / wide: 2^32 - 5, 2 parties,
-    // width 64 2.8 / 7.4, 32768 (two blocks) 4.9 / 7.6, 50000 8.6 / 7.7, 65536 (four) 9.6 / 8.2; 2^61 - 1,
-    // 2 parties, 32768 6.9 / 9.0, 65536 13.7 / 9.9, 3 parties, 16384 (two) 7.5 / 12.6, 32768 13.8 / 12.9.
-    int operands = 0;
-    for (int q = 0; q < nins; q++) operands += fused_operands(ins[q].kind, ins[q].flags);
-    const int64_t blocks = narrow_blocks(c, W);
-    if (blocks > 0 && narrow_fits(c, nslots, operands, blocks)) {
-      NarrowArgs<F, N> A;
-      A.nins = nins;
-      A.nbase = 0;
-      A.nslots = nslots;
-      for (int q = 0; q < nins; q++) {
-        FusedIns I = ins[q];
-        const u64 *p[3] = {I.p0, I.p1, I.p2};
-        const bool pub = I.kind == FK_PUBADD || I.kind == FK_PUBMUL;
-        const u64 mark = !pub ? 0 : (I.flags & FF_PUB_VEC) ? NB_PUB | NB_VEC : NB_PUB;
-        I.reads = (uint8_t)fused_operands(I.kind, I.flags);
-        for (int o = 0; o < I.reads; o++) A.base[A.nbase++] = (u64)(uintptr_t)p[o] | mark;
-        std::memcpy(&A.ins[q].fields, &I, 8);
-        A.ins[q].out = I.out;
-        A.ins[q].j = I.j;
-      }
-      A.W = W;
-      alpha_of<F, N>(c, A.alpha);
-      A.coef_state = coef_state(c);
-      A.acc = c->d_acc;
-      KTimer tm(c, "fused");
-      hipLaunchKernelGGL((k_fused_narrow<F, N>), dim3((unsigned)blocks), dim3(BLOCK),
-                         (size_t)narrow_bytes(c, nslots, operands), c->stream, A);
-      spdz_status s = hip_status(hipGetLastError());
-      if (s == SPDZ_OK && blocks > c->slots) c->slots = (int)blocks;
-      return s;
-    }
-    if (nslots > fused_max_slots(c->n, c->L, c->fid)) return SPDZ_E_INVAL;
-    FusedArgs<F, N> A;
-    for (int q = 0; q < nins; q++) A.ins[q] = ins[q];
-    A.nins = nins;
-    A.W = W;
-    alpha_of<F, N>(c, A.alpha);
-    A.coef_state = coef_state(c);
-    A.acc = c->d_acc;
-    const size_t lds = (size_t)nslots * 2 * N * F::L * fused_word_bytes(c->fid) * BLOCK;
-    const void *k = (const void *)k_fused<F, N>;
-    const int g = grid_for(c, k, W);
-    KTimer tm(c, "fused");
-    hipLaunchKernelGGL((k_fused<F, N>), dim3(g), dim3(BLOCK), lds, c->stream, A);
-    spdz_status s = hip_status(hipGetLastError());
-    if (s == SPDZ_OK && g > c->slots) c->slots = g;
-    return s;
+    // (no list is made where a thread's slots are too few, so no kernel either)
+    constexpr int word = sizeof(typename F::E) == 4 ? 4 : 8;
+    if constexpr (FUSED_LDS_BYTES / (2 * N * F::L * word * BLOCK) < FUSED_MIN_SLOTS) return SPDZ_E_UNSUPPORTED;
+    else return launch_list<F, N>(c, ins, nins, nslots, W);
   });
 }
 

@@ -686,7 +686,7 @@ void build_groups(spdz_prog *g) {
         continue;
       }
       const int maxs = fused_slots(g->c, N[lines[i]].width);
-      if (maxs < 3) return;  // a product needs its two operands and its result
+      if (maxs < FUSED_MIN_SLOTS) return;  // (of the field and the number of parties, whatever the width)
       std::vector<int> run;
       FGroup G, trial;
       for (size_t j = i; j < lines.size() && fusable(g, N[lines[j]]) && N[lines[j]].width == N[lines[i]].width; j++) {
