@@ -41,7 +41,7 @@ __device__ __forceinline__ void dot64(const float (&w)[HID], const float *hs, fl
 
 // Lane j of a wave is neuron j of each layer; activations pass between layers through the wave's own
 // LDS rows, read by all lanes at once.  Bound at small batches by reading the weights and a chain of
-// about 210 multiply-adds: 10 us at batch 32, where one thread per sample with its activations in
+// about 210 multiply-adds: 6 us at batch 32, where one thread per sample with its activations in
 // scratch memory took 41-45.
 __global__ __launch_bounds__(256) void k_mlp_forward(const float *__restrict__ W, const float *__restrict__ X,
                                                      int64_t B, float *__restrict__ Y, float *__restrict__ acts) {
@@ -156,9 +156,9 @@ __global__ __launch_bounds__(256) void k_mlp_predict(const float *__restrict__ W
 // over the chunks of CHUNK samples this block takes, into out + blockIdx.x NPARAM.  Per chunk the 8
 // waves form the deltas of the pre-activations they need (lane k sums column k of the weights), the
 // block then its group's outer products, a thread eight of them, samples in ascending order.
-// A block keeps the deltas on chip: 10 us at batch 32 (58 at 8192; 12 with the samples' LDS reads one at a
-// time), where deltas by one thread per
-// sample (43-47 us) and products by one thread per parameter (11; 2300 at 8192) met in memory.
+// A block keeps the deltas on chip: 10 us at batch 32 (12 with the samples' LDS reads one at a time; 25 at 8192, then
+// 30 for the sum of the parts), where deltas by one thread per sample (43-47 us) and products by one thread per
+// parameter (11; 2300 at 8192) met in memory.
 constexpr int CHUNK = 64;
 __global__ __launch_bounds__(512) void k_mlp_backward(const float *__restrict__ W, const float *__restrict__ X,
                                                       const float *__restrict__ acts, const float *__restrict__ dY,
